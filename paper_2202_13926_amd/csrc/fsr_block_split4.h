@@ -1,81 +1,169 @@
-// fsr_block_split4.h -- one S = 32 support block of the sequential variant
-// (the original FSR that Sec. II departs from) on four wavefronts.
+// fsr_block_split4.h -- one S = 32 support block on a workgroup of four
+// wavefronts, for calls that hold too few blocks to fill the device: small
+// images, and the sequential variant (the original FSR that Sec. II departs
+// from), whose blocks depend on one another.  Such a call is bound by the
+// latency of a block, i.e. by the chain of its iterations.
 //
-// The variant runs one launch per wavefront step of its schedule, and a step
-// holds at most a few hundred blocks: with one wavefront per block most
-// SIMDs idle and each block's time is the latency of one wavefront alone.
-// Here a workgroup of four wavefronts takes one block.  Wavefront 0 runs
-// the gather, the mean split and the forward transforms exactly as
-// fsr_block.h does (kDftFft32, kReuse), then parks bins of slots 4..15 and
-// the W table in LDS; wavefront q keeps slots 4q .. 4q + 3 (bins
-// (2s + h, c)) for the iterations.  Per iteration each wavefront reduces its
-// own 256 keys (same keys, same tie codes 15 - s) to a candidate (key,
-// lane, R_w at the winner), the four candidates meet in LDS behind one
-// workgroup barrier (double-buffered, so one barrier per iteration
-// suffices), and every wavefront takes the largest: the same bin as the
-// one-wavefront routine, whose keys are unique across slots.  Each bin's
-// residual update is the same arithmetic in the same order, and every
-// wavefront accumulates the target model as before (wavefront 0 writes
-// it), so the result is bitwise that of the one-wavefront routine.
+// Wavefront q keeps the bins of slots NS q .. NS q + NS - 1 (bins (2s + h, c),
+// NS = 4) in registers and a copy of R_w in LDS; W lies in LDS with every row
+// repeated (one offset per iteration; residency does not matter here).  Per
+// iteration each lane puts its largest key (the same keys and tie codes
+// 15 - s as in fsr_block.h) into LDS, and behind one workgroup barrier (keys
+// and R_w are double-buffered, so one suffices) every wavefront reduces all
+// four wavefronts' keys itself: over the wavefronts per lane, then over the
+// lanes.  That is one cross-lane reduction on the chain; reducing per
+// wavefront first and then over the four candidates has two.  R_w at the
+// winner is read with the W rows, in the same LDS wait.  The set-up is spread
+// over the wavefronts too: each gathers four of the sixteen row pairs, all
+// loads at once, and takes one radix-4 column of the FFT passes.
+//
+// Every value is computed by the same operations in the same order as in
+// fsr_block.h (kDftFft32), so the result is bitwise that of the
+// one-wavefront routine.
+//
+// Measured (64 x 64 frame, 256 blocks, I = 100): 41.2 us a call against 47.8
+// with one wavefront per block (322 against 393 ns an iteration) and 43.8
+// with the two-stage reduction; eight wavefronts per block 44.5.  A step of
+// the sequential variant at VGA: 23.4 us at I = 50 against 29.2 before, of
+// which the set-up (I = 0) 4.8 against 8.7 us.
 #pragma once
 
 #include "fsr_block.h"
+#include "fsr_block_sg.h"
 
 namespace fsr {
 
-// Four residual bins as one register tuple, for the indexed read of the
-// winner's slot.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kSplitWaves = 4;
+constexpr int kSplitSlots = kSlots / kSplitWaves;   // slots per wavefront
 
-// LDS of the routine beyond the block's kLdsFloats: bins of slots 4..15
-// (12 x 64 float2), two buffers of four candidates, the "any pixel known"
-// flag.
-struct Split4Lds {
-    float2 bins[12 * 64];
-    uint4 cand[2][4];
-    int any_known;
+// Calls (or steps) of at most this many blocks, two per compute unit, take
+// this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 576
+// blocks: here 41.2 / 45.6 / 46.2 / 55.5, one wavefront per block 47.8 / 48.4 /
+// 48.5 / 48.7 (a third workgroup on a compute unit costs more than the
+// latency it saves: every wavefront repeats the reduction).
+constexpr int64_t kSplitMaxBlocks = 512;
+
+// LDS of a workgroup: the W table with its rows repeated (row r at r and
+// r + 32); the transpose planes, before them the gathered tile; the exchange
+// area of the FFT passes; two buffers of R_w by slot and of the lanes' keys;
+// flags.
+struct SplitLds {
+    float2 w[2 * kS * kS];
+    union {
+        float planes[2 * kS * Planes::kPitch];
+        float2 tile[kSlots * 64];   // (f~, w) of slot s, lane
+    };
+    float2 ex[16 * 64];
+    float2 r[2][kSlots][64];
+    uint32_t key[2][kSplitWaves][64];
+    int known[kSplitWaves];
 };
 
-__device__ __forceinline__ void reconstruct_block_reuse_split4(const BlockJob& jb, int B, int L, float gamma,
-                                                               const BlockTables& tab, float* lds,
-                                                               Split4Lds& sh) {
+// One 32-point DFT pass of dft32_lane_pair on four wavefronts: z[j] of
+// wavefront q holds slot q + 4 j on entry (element s = 4 j + q of the lane's
+// sequence) and output k' = q + 4 j on return (bin k' + 16 h of the pass).
+// The radix-4 x 4 transform's first stage takes the column s2 = q, its second
+// the row k1 = q; the 16 values meet in ex in between.
+__device__ __forceinline__ void split_dft32_pass(float (&re)[4], float (&im)[4], float2* ex, int q, int lane) {
+    const int h = lane >> 5;
+    dft4_slots(re, im);
+    if (q != 0) {
+#pragma unroll
+        for (int k1 = 1; k1 < 4; ++k1) cmul(re[k1], im[k1], kTw.re[(2 * k1 * q) & 31], kTw.im[(2 * k1 * q) & 31]);
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) ex[(4 * k1 + q) * 64 + lane] = make_float2(re[k1], im[k1]);
+    __syncthreads();
+#pragma unroll
+    for (int s2 = 0; s2 < 4; ++s2) {
+        const float2 v = ex[(4 * q + s2) * 64 + lane];
+        re[s2] = v.x;
+        im[s2] = v.y;
+    }
+    dft4_slots(re, im);
+    const float sgn = h ? -1.0f : 1.0f;
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) {
+        const int k = q + 4 * k2;
+        float er, ei, orr, oi;
+        split_halves(re[k2], er, orr);
+        split_halves(im[k2], ei, oi);
+        cmul(orr, oi, kTw.re[k], kTw.im[k]);
+        re[k2] = fmaf(sgn, orr, er);
+        im[k2] = fmaf(sgn, oi, ei);
+    }
+}
+
+// kReuse: as in fsr_block.h.
+template <bool kReuse>
+__device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int B, int L, float gamma,
+                                                        const BlockTables& tab, SplitLds& sh) {
+    constexpr int NS = kSplitSlots;
     const int lane = (int)(threadIdx.x & 63);
     const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wavefront of the block
     const int c = lane & 31, h = lane >> 5;
     const int ti = lane / B, tj = lane - (lane / B) * B;
     const int tm = L + ti, tn = L + tj;
-    float2* wtab = reinterpret_cast<float2*>(lds);
-    f32x4 vr = {}, vi = {};
 
-    if (q == 0) {
-        // ---- gather and weighting, pixel (m, n) = (2s + h, c); earlier
-        // targets (the rows above this target, and this target's rows left
-        // of it) take part with their reconstruction
+    // ---- gather and weighting, pixel (m, n) = (2s + h, c) of slots
+    // 4q .. 4q + 3; all loads go out together (an address that holds nothing
+    // of use reads pixel 0)
+    {
         const int y0 = jb.by * B - L, x0 = jb.bx * B - L;
-        float xr[16], wr[16];
-        uint64_t any_known = 0;
         const int x = x0 + c;
         const bool xin = (unsigned)x < (unsigned)jb.width;
+        uint8_t kraw[NS];
+        float fraw[NS], rp[NS], old[NS];
+        bool in[NS], earlier[NS];
 #pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const int m = 2 * s + h, y = y0 + m;
-            const bool in = xin && (unsigned)y < (unsigned)jb.height;
-            const int64_t off = in ? (int64_t)y * jb.stride + x : 0;
-            const uint8_t kraw = jb.mask[off];
-            const float fraw = jb.image[off];
-            const float rp = global_ptr(tab.rho_pow)[m * kS + c];
-            const uint8_t k = in ? kraw : (uint8_t)0;
-            const float w = k ? rp : 0.0f;
-            const bool earlier = m < L || (m < L + B && c < L);
-            const bool reused = in && !k && earlier && jb.delta > 0.0f;
-            any_known |= ballot(k != 0 || reused);
-            xr[s] = k ? fraw : reused ? (float)jb.out[off] : 0.0f;
-            wr[s] = reused ? jb.delta * rp : w;
+        for (int j = 0; j < NS; ++j) {
+            const int m = 2 * (NS * q + j) + h, y = y0 + m;
+            in[j] = xin && (unsigned)y < (unsigned)jb.height;
+            const int64_t off = in[j] ? (int64_t)y * jb.stride + x : 0;
+            kraw[j] = jb.mask[off];
+            fraw[j] = jb.image[off];
+            rp[j] = global_ptr(tab.rho_pow)[m * kS + c];
+            if constexpr (kReuse) {
+                earlier[j] = in[j] && (m < L || (m < L + B && c < L));
+                old[j] = jb.out[earlier[j] ? off : 0];
+            }
         }
-        if (any_known != 0) {
-            // ---- R_w = mu W + DFT2((f~ - mu) w) and W, both real tiles in
-            // one complex FFT, as in fsr_block.h
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const uint8_t k = in[j] ? kraw[j] : (uint8_t)0;
+            float f = k ? fraw[j] : 0.0f, w = k ? rp[j] : 0.0f;
+            bool takes = k != 0;
+            if constexpr (kReuse) {
+                const bool reused = earlier[j] && !k && jb.delta > 0.0f;
+                f = reused ? old[j] : f;
+                w = reused ? jb.delta * rp[j] : w;
+                takes = takes || reused;
+            }
+            any |= ballot(takes);
+            sh.tile[(NS * q + j) * 64 + lane] = make_float2(f, w);
+        }
+        if (lane == 0) sh.known[q] = any != 0;
+    }
+    __syncthreads();
+    const bool any_known = (sh.known[0] | sh.known[1] | sh.known[2] | sh.known[3]) != 0;
+
+    float acc = 0.0f;
+    const int iters = jb.iterations;
+    if (any_known) {
+        // ---- R_w = mu W + DFT2((f~ - mu) w) and W, both real tiles in one
+        // complex FFT, as in fsr_block.h; every wavefront forms the sums and
+        // the scale itself
+        float zr[4], zi[4], mu, scale, xmax;
+        {
+            float xr[16], wr[16];
             float sx = 0.0f, sw = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const float2 v = sh.tile[64 * s + lane];
+                xr[s] = v.x;
+                wr[s] = v.y;
+            }
 #pragma unroll
             for (int s = 0; s < 16; ++s) {
                 sx = fmaf(xr[s], wr[s], sx);
@@ -83,121 +171,118 @@ __device__ __forceinline__ void reconstruct_block_reuse_split4(const BlockJob& j
             }
             sx = wave_sum_f32(sx);
             sw = wave_sum_f32(sw);
-            const float mu = sw > 0.0f ? sx / sw : 0.0f;
+            mu = sw > 0.0f ? sx / sw : 0.0f;
 #pragma unroll
             for (int s = 0; s < 16; ++s) xr[s] = (xr[s] - mu) * wr[s];
-            float xi[16], wi[16];
-            float scale;
-            const float xmax = max_abs_and_scale(xr, scale);
-#pragma unroll
-            for (int s = 0; s < 16; ++s) xi[s] = wr[s] * scale;
-            dft2_complex_to_planes(xr, xi, lds, lane);
-            planes_split_two_real(xr, xi, wr, wi, 0.5f / scale, lds, lane);
-            if (xmax == 0.0f) {
-#pragma unroll
-                for (int s = 0; s < 16; ++s) xr[s] = xi[s] = 0.0f;
-            }
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                xr[s] = fmaf(mu, wr[s], xr[s]);
-                xi[s] = fmaf(mu, wi[s], xi[s]);
-            }
-            // W with duplicated rows, as in fsr_block.h; slots 4..15 parked
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                const int k = 2 * s + h;
-                wtab[k * kS + c] = make_float2(wr[s], wi[s]);
-                wtab[(k + kS) * kS + c] = make_float2(wr[s], wi[s]);
-            }
-#pragma unroll
-            for (int s = 4; s < 16; ++s) sh.bins[64 * (s - 4) + lane] = make_float2(xr[s], xi[s]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                vr[s] = xr[s];
-                vi[s] = xi[s];
-            }
+            xmax = max_abs_and_scale(xr, scale);
         }
-        if (lane == 0) sh.any_known = any_known != 0;
-    }
-    __syncthreads();
-
-    float acc = 0.0f;
-    const int iters = jb.iterations;
-    if (sh.any_known) {
-        if (q != 0) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float2 v = sh.bins[64 * (4 * q - 4 + s) + lane];
-                vr[s] = v.x;
-                vi[s] = v.y;
-            }
+        for (int j = 0; j < 4; ++j) {
+            const float2 v = sh.tile[64 * (q + 4 * j) + lane];
+            zr[j] = (v.x - mu) * v.y;
+            zi[j] = v.y * scale;
         }
-        const float w00 = wtab[0].x;   // W[0][0]: row 0, column 0
-        const float gi = w00 > 0.0f ? gamma / w00 : 0.0f;
-        float wf[4];
+        float* pr = Planes::re(sh.planes);
+        float* pi = Planes::im(sh.planes);
+        split_dft32_pass(zr, zi, sh.ex, q, lane);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) wf[s] = global_ptr(tab.freq_w)[(2 * (4 * q + s) + h) * kS + c];
+        for (int j = 0; j < 4; ++j) {
+            pr[Planes::idx(q + 4 * j + 16 * h, c)] = zr[j];
+            pi[Planes::idx(q + 4 * j + 16 * h, c)] = zi[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            zr[j] = pr[Planes::idx(c, 2 * (q + 4 * j) + h)];
+            zi[j] = pi[Planes::idx(c, 2 * (q + 4 * j) + h)];
+        }
+        split_dft32_pass(zr, zi, sh.ex, q, lane);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            pr[Planes::idx(c, q + 4 * j + 16 * h)] = zr[j];
+            pi[Planes::idx(c, q + 4 * j + 16 * h)] = zi[j];
+        }
+        __syncthreads();
+        // ---- the two spectra of this wavefront's slots; W into the table
+        float vr[NS], vi[NS], wf[NS];
+        const float half_inv_s = 0.5f / scale;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int k = 2 * (NS * q + s) + h, km = (kS - k) & 31, lm = (kS - c) & 31;
+            const float ar = pr[Planes::idx(k, c)], ai = pi[Planes::idx(k, c)];
+            const float br = pr[Planes::idx(km, lm)], bi = pi[Planes::idx(km, lm)];
+            const float xr = xmax == 0.0f ? 0.0f : 0.5f * (ar + br);
+            const float xi = xmax == 0.0f ? 0.0f : 0.5f * (ai - bi);
+            const float wr = (ai + bi) * half_inv_s, wi = (br - ar) * half_inv_s;
+            vr[s] = fmaf(mu, wr, xr);
+            vi[s] = fmaf(mu, wi, xi);
+            wf[s] = global_ptr(tab.freq_w)[k * kS + c];
+            sh.w[k * kS + c] = make_float2(wr, wi);
+            sh.w[(k + kS) * kS + c] = make_float2(wr, wi);
+        }
         const int tw_re = __float_as_int(kTw.re[c]), tw_im = __float_as_int(kTw.im[c]);
         const int tmn4 = opaque((4 * tm) | ((4 * tn) << 16));
         // byte offset of the lane's entry (h, c) in W, plus this wavefront's
         // first slot (512 bytes per slot): the low byte stays 8 c
-        const int hc8 = opaque(256 * h + 8 * c + 2048 * q);
-        const uint32_t code0 = 15u - 4u * (uint32_t)q;
+        const int hc8 = opaque(256 * h + 8 * c + 512 * NS * q);
+        const uint32_t code0 = 15u - (uint32_t)(NS * q);
+        __syncthreads();
+        const float w00 = sh.w[0].x;
+        const float gi = w00 > 0.0f ? gamma / w00 : 0.0f;
 
+        // R_w of this wavefront's slots, for the wavefronts that need the winner's
+#pragma unroll
+        for (int s = 0; s < NS; ++s) sh.r[0][NS * q + s][lane] = make_float2(vr[s], vi[s]);
         for (int it = 0; it < iters; ++it) {
-            // this wavefront's candidate: its largest key (Eq. 16, the same
-            // keys as the one-wavefront routine), lane and R_w
+            const int buf = it & 1;
+            // this wavefront's largest key of each lane (Eq. 16, the same keys
+            // as the one-wavefront routine)
             uint32_t lmax = 0;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < NS; ++s) {
                 const float e = fmaf(vr[s], vr[s], vi[s] * vi[s]);
                 const uint32_t key = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | (code0 - (uint32_t)s);
                 lmax = umax(lmax, key);
             }
+            sh.key[buf][q][lane] = lmax;
+            __syncthreads();
+            // every wavefront reduces all keys: over the wavefronts, then the
+            // lanes; equal keys go to the lower lane
+#pragma unroll
+            for (int w = 0; w < kSplitWaves; ++w) lmax = umax(lmax, sh.key[buf][w][lane]);
             const uint32_t mx = wave_max_u32(lmax);
             const int ln = (int)__builtin_ctzll(ballot(lmax == mx));
-            const int sl = (int)(code0 - (mx & 15u));   // slot within this wavefront
-            const float pr_q = readlane_f(vr[sl], ln);
-            const float pi_q = readlane_f(vi[sl], ln);
-            uint4* cb = sh.cand[it & 1];
-            if (lane == 0) cb[q] = make_uint4(mx, (uint32_t)ln, __float_as_uint(pr_q), __float_as_uint(pi_q));
-            __syncthreads();
-            // the largest of the four (keys differ: each slot has its own code)
-            const uint4 cq = cb[lane & 3];
-            uint32_t best = umax(cq.x, dpp_u32<0xB1>(cq.x));
-            best = umax(best, dpp_u32<0x4E>(best));
-            const int qw = (int)__builtin_ctzll(ballot(cq.x == best));   // lanes 0..3 hold wavefronts 0..3
-            const uint32_t mxw = (uint32_t)__builtin_amdgcn_readlane((int)cq.x, qw);
-            const int lnw = __builtin_amdgcn_readlane((int)cq.y, qw);
-            const float pr = __int_as_float(__builtin_amdgcn_readlane((int)cq.z, qw));
-            const float pim = __int_as_float(__builtin_amdgcn_readlane((int)cq.w, qw));
-            const int idx = 64 * (15 - (int)(mxw & 15u)) + lnw;
+            const int slot = 15 - (int)(mx & 15u);
+            const int idx = 64 * slot + ln;
             const int u = idx >> 5, v = idx & 31;
-            const float cr = gi * pr, ci = gi * pim;    // gamma * p (Eqs. 10-11)
+            const float2 rw = sh.r[buf][slot][ln];
             // residual (Eqs. 12, 14-15) on this wavefront's slots, as in
-            // fsr_block.h: slot 4q + s reads duplicated row h + 32 - u +
-            // 2 (4q + s), column (c - v) mod 32.  The reads go out first so
-            // that the model's lane exchange waits alongside them.
+            // fsr_block.h.  The reads go out first; the model's lane exchange
+            // is used after the update
             const int woff = sub_low_byte(hc8 + (8192 - 256 * u), 8 * v);
-            const float2* wrow = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(wtab) + woff);
-            float2 w[4];
+            const float2* wrow = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(sh.w) + woff);
+            float2 w[NS];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) w[s] = wrow[64 * s];
+            for (int s = 0; s < NS; ++s) w[s] = wrow[64 * s];
+            __builtin_amdgcn_sched_barrier(0);
             // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target;
             // every wavefront computes it (no branch in the loop's chain),
             // wavefront 0's is the one written
             const int q4 = dot2_u16(u | (v << 16), tmn4);
             const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_re));
             const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_im));
-            acc = fmaf(cr, er, acc);
-            acc = fmaf(ci, ei, acc);
+            const float cr = gi * rw.x, ci = gi * rw.y;    // gamma * p (Eqs. 10-11)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < NS; ++s) {
                 vr[s] = fmaf(-cr, w[s].x, vr[s]);
                 vr[s] = fmaf(ci, w[s].y, vr[s]);
                 vi[s] = fmaf(-cr, w[s].y, vi[s]);
                 vi[s] = fmaf(-ci, w[s].x, vi[s]);
+                sh.r[buf ^ 1][NS * q + s][lane] = make_float2(vr[s], vi[s]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            acc = fmaf(cr, er, acc);
+            acc = fmaf(ci, ei, acc);
             if (q == 0 && jb.log != nullptr && lane == 0) jb.log[it] = (uint16_t)idx;
         }
     } else if (q == 0 && jb.log != nullptr) {

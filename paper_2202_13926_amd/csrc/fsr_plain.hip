@@ -1,6 +1,7 @@
 // fsr_plain.hip -- one-image FSR at S = 32: one workgroup of one wavefront
-// per block.  Supports 8, 16 and 24 are in fsr_plain_sg.hip.
+// per block, or of four for the smallest images (fsr_block_split4.h).  Supports 8, 16 and 24 are in fsr_plain_sg.hip.
 #include "fsr_block.h"
+#include "fsr_block_split4.h"
 
 namespace fsr {
 
@@ -12,6 +13,13 @@ __global__ __launch_bounds__(64) void fsr_plain_s32(PlainLaunch p) {
                                      reinterpret_cast<uint2*>(lds + kLdsFloats));
 }
 
+// The same with kSplitWaves wavefronts per block (fsr_block_split4.h).
+__global__ __launch_bounds__(64 * kSplitWaves) void fsr_plain_split_s32(PlainLaunch p) {
+    __shared__ __align__(16) SplitLds sh;
+    const int64_t blk = xcd_contiguous(blockIdx.x, p.n_blocks);
+    reconstruct_block_split<false>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, sh);
+}
+
 hipError_t launch_plain(const PlainLaunch& p, hipStream_t stream) {
     if (p.n_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)p.n_blocks), block(64);
@@ -21,6 +29,8 @@ hipError_t launch_plain(const PlainLaunch& p, hipStream_t stream) {
         hipLaunchKernelGGL((fsr_plain_s32<kDftFft32, kArgmaxLds>), grid, block, 0, stream, p);
     } else if (p.dft == kDftSplitBf16) {
         hipLaunchKernelGGL((fsr_plain_s32<kDftSplitBf16, kArgmaxWave>), grid, block, 0, stream, p);
+    } else if (p.n_blocks <= kSplitMaxBlocks) {
+        hipLaunchKernelGGL(fsr_plain_split_s32, grid, dim3(64 * kSplitWaves), 0, stream, p);
     } else {
         hipLaunchKernelGGL((fsr_plain_s32<kDftFft32, kArgmaxWave>), grid, block, 0, stream, p);
     }

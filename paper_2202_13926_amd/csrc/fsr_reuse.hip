@@ -39,13 +39,12 @@ __global__ __launch_bounds__(64) void fsr_reuse_s32(PlainLaunch p, float delta, 
     reconstruct_block<kDftFft32, kArgmaxWave, false, true>(jb, p.block, p.border, p.gamma, p.tab, lds);
 }
 
-// The same blocks with four wavefronts each (fsr_block_split4.h), for steps
-// too small to fill the device; bitwise the same result.
-__global__ __launch_bounds__(256) void fsr_reuse_split4_s32(PlainLaunch p, float delta, int32_t step,
+// The same blocks with four wavefronts each, for steps of at most
+// kSplitMaxBlocks blocks over all frames; bitwise the same result.
+__global__ __launch_bounds__(64 * kSplitWaves) void fsr_reuse_split4_s32(PlainLaunch p, float delta, int32_t step,
                                                             int32_t by_lo, int32_t slope, int64_t frame_stride,
                                                             int64_t log_stride) {
-    __shared__ __align__(16) float lds[kLdsFloats];
-    __shared__ Split4Lds sh;
+    __shared__ __align__(16) SplitLds sh;
     const int by = by_lo + (int)blockIdx.x;
     const int bx = step - slope * by;
     const int64_t f = blockIdx.y;
@@ -55,15 +54,8 @@ __global__ __launch_bounds__(256) void fsr_reuse_split4_s32(PlainLaunch p, float
     jb.out += f * frame_stride;
     if (jb.log != nullptr) jb.log += f * log_stride;
     jb.delta = delta;
-    reconstruct_block_reuse_split4(jb, p.block, p.border, p.gamma, p.tab, lds, sh);
+    reconstruct_block_split<true>(jb, p.block, p.border, p.gamma, p.tab, sh);
 }
-
-// Steps with at most this many blocks (over all frames) run four wavefronts
-// per block.  Measured on 1080p frames (at most 96 blocks per step and
-// frame), ms per call of 1 / 2 / 3 / 4 / 8 frames: one wavefront per block
-// 105.4 / 105.8 / 107.5 / 108.1 / 108.8; four for every step 92.0 / 92.0 /
-// 97.8 / 99.1 / 110.7.
-constexpr int64_t kSplit4MaxBlocks = 512;
 
 int64_t reuse_steps(int32_t height, int32_t width, int32_t block, int32_t border) {
     const int64_t nby = (height + block - 1) / block, nbx = (width + block - 1) / block;
@@ -85,8 +77,8 @@ hipError_t launch_reuse(const PlainLaunch& p, float delta, int32_t n_frames, int
         const int64_t hi = std::min<int64_t>(nby - 1, t / slope);
         if (hi < lo) continue;   // no block at this step (possible when slope > nbx)
         const dim3 grid((unsigned)(hi - lo + 1), (unsigned)n_frames);
-        if ((hi - lo + 1) * (int64_t)n_frames <= kSplit4MaxBlocks)
-            hipLaunchKernelGGL(fsr_reuse_split4_s32, grid, dim3(256), 0, stream, p, delta, (int32_t)t,
+        if ((hi - lo + 1) * (int64_t)n_frames <= kSplitMaxBlocks)
+            hipLaunchKernelGGL(fsr_reuse_split4_s32, grid, dim3(64 * kSplitWaves), 0, stream, p, delta, (int32_t)t,
                                (int32_t)lo, (int32_t)slope, frame_stride, log_stride);
         else
             hipLaunchKernelGGL(fsr_reuse_s32, grid, dim3(64), 0, stream, p, delta, (int32_t)t, (int32_t)lo,
