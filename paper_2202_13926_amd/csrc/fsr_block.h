@@ -18,13 +18,22 @@
 //              (Eqs. 12, 14-15)
 //   compose    known target pixels copied, unknown ones take Re g
 //
-// LDS: 16 KiB per wavefront.  The weight spectrum W is stored with its 32
-// rows duplicated (64 rows x 32 bins x float2) so that the rows a lane needs
-// for its 16 bins, (k - u) mod 32 for k = 2s + h, form one contiguous run and
-// every slot's address is the lane's base plus an immediate offset.  The
-// same buffer first serves as the transpose scratch of the FFTs, or, in the
-// matrix-core variant, holds the first spectrum (upper half) while the
-// second is transformed.
+// LDS: 9.75 KiB per wavefront.  The weight spectrum W is stored with seven of
+// its 32 rows repeated (39 rows x 32 bins x float2): the rows a lane needs for
+// four neighbouring slots, (k - u) mod 32 for k = 2s + h, then form one run,
+// read from one address with immediate offsets, and only the four groups'
+// addresses depend on u (w_group_offset).  The table's size decides the
+// kernel: the loop's instructions would issue in about 390 cycles per SIMD
+// and iteration, and with all 32 rows repeated (16 KiB, 10 wavefronts per
+// compute unit, no address select) it took 582, waiting.  Wavefronts per
+// compute unit, by padding the table, us per 1080p frame at I = 100: 8 3519,
+// 10 3450, 12 3025, 14 2792, 16 2692.  This table holds 16, what the kernel's
+// 128 registers allow: 3439 -> 2798 us with the selects (set-up alone 374 ->
+// 275).  Three repeated rows (8.75 KiB, eight groups) gain no wavefront and
+// measured 2849; 96 registers and 18 wavefronts spill, 2951.
+// The same buffer first serves as the transpose scratch of the FFTs, or, in
+// the matrix-core variant, holds the first spectrum while the second is
+// transformed.
 #pragma once
 
 #include <type_traits>
@@ -292,12 +301,7 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
         // support with one known pixel), and as R_w shrinks the error of the
         // early iterations would take over the argmax
         float2* wtab = reinterpret_cast<float2*>(lds);
-#pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const int k = 2 * s + h;
-            wtab[k * kS + c] = make_float2(wr[s], wi[s]);
-            wtab[(k + kS) * kS + c] = make_float2(wr[s], wi[s]);
-        }
+        store_w_table(wr, wi, wtab, c, h);
         const float w00 = readlane_f(wr[0], 0);
         const float gi = w00 > 0.0f ? gamma / w00 : 0.0f;
         float wf[16];
@@ -387,24 +391,32 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
                 }
 
                 // residual: R_w[k,l] -= gamma p W[(k-u) mod S, (l-v) mod S]; slot s
-                // reads duplicated row h + 32 - u + 2s (rows 1 .. 63 of the
-                // table), column (c - v) mod 32: byte offset 256 (h + 32 - u) +
-                // 8 ((c - v) mod 32) + 512 s.  All sixteen reads go out before
-                // the model's lane exchange and are waited for together: issued
-                // a pair at a time behind the exchange (the compiler's order
-                // otherwise), their latency showed through the 2.5 wavefronts
-                // per SIMD that the table's LDS leaves, 3.75 against 3.48 ms
-                // per 1080p frame
-                const int woff = sub_low_byte(hc8 + (8192 - 256 * u), 8 * v);
-                const float2* wrow = reinterpret_cast<const float2*>(
-                    reinterpret_cast<const char*>(wtab) + woff);
+                // reads row 2s + h - u (mod 32), column (c - v) mod 32: byte
+                // offset 256 (2s + h - u) + 8 ((c - v) mod 32), the rows of a
+                // group of four slots from one address.  All sixteen reads go
+                // out before the model's lane exchange and are waited for
+                // together
+                const int woff = sub_low_byte(hc8 + kWRowBytes * (kWLead - u), 8 * v);
                 float2 wv[16];
 #pragma unroll
-                for (int s = 0; s < 16; ++s) wv[s] = wrow[64 * s];
+                for (int g = 0; g < 4; ++g) {
+                    const float2* wrow = reinterpret_cast<const float2*>(
+                        reinterpret_cast<const char*>(wtab) + (woff + w_group_offset(g, u)));
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) wv[4 * g + j] = wrow[64 * j];
+                }
                 // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target
                 const int q4 = dot2_u16(u | (v << 16), tmn4);
                 const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_re));
                 const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_im));
+#pragma unroll
+                for (int s = 0; s < 16; ++s) {
+                    const float2 w = wv[s];
+                    vr[s] = fmaf(-cr, w.x, vr[s]);
+                    vr[s] = fmaf(ci, w.y, vr[s]);
+                    vi[s] = fmaf(-cr, w.y, vi[s]);
+                    vi[s] = fmaf(-ci, w.x, vi[s]);
+                }
                 if constexpr (kDft == kDftSplitBf16) {
                     // compensated sum of the I model terms
                     const float y = fmaf(cr, er, ci * ei) - acc_comp;
@@ -414,15 +426,6 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
                 } else {
                     acc = fmaf(cr, er, acc);
                     acc = fmaf(ci, ei, acc);
-                }
-
-#pragma unroll
-                for (int s = 0; s < 16; ++s) {
-                    const float2 w = wv[s];
-                    vr[s] = fmaf(-cr, w.x, vr[s]);
-                    vr[s] = fmaf(ci, w.y, vr[s]);
-                    vi[s] = fmaf(-cr, w.y, vi[s]);
-                    vi[s] = fmaf(-ci, w.x, vi[s]);
                 }
             }
         };

@@ -20,7 +20,34 @@ namespace fsr {
 constexpr int kSlots = 16;        // bins (or pixels) per lane
 
 // ---------------------------------------------------------------- LDS of a block
-constexpr int kLdsFloats = 2 * 64 * kS;   // 4096 floats = 16 KiB
+// W table: rows -kWLead .. 31 of the weight spectrum, row r at index
+// r + kWLead (kWLead repeated rows, see w_group_offset), 32 float2 each.
+constexpr int kWLead = 7;
+constexpr int kWRowBytes = 8 * kS;
+constexpr int kLdsFloats = 2 * kS * (kS + kWLead);   // 2496 floats = 9.75 KiB
+
+// Writes W[k][c] of the slots s (k = 2s + h) into the table; rows 25..31
+// also as rows -7..-1.
+__device__ __forceinline__ void store_w_table(const float (&wr)[kSlots], const float (&wi)[kSlots],
+                                              float2* wtab, int c, int h) {
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) {
+        const int k = 2 * s + h;
+        const float2 w = make_float2(wr[s], wi[s]);
+        wtab[(k + kWLead) * kS + c] = w;
+        if (2 * s + 1 >= kS - kWLead && k >= kS - kWLead) wtab[(k + kWLead - kS) * kS + c] = w;
+    }
+}
+
+// Byte offset that slots 4g .. 4g + 3 add to the lane's W address.  Slot s
+// needs row 2s + h - u (mod 32); with the seven repeated rows, a group of
+// four slots is read without a wrap inside it: the groups below u / 8 lie
+// wholly one table (32 rows) up, the others start at row -7 at the lowest
+// (s = 4 (u / 8), h = 0, u mod 8 = 7).  u is wave-uniform, so this is scalar
+// arithmetic.
+__device__ __forceinline__ int w_group_offset(int g, int u) {
+    return g < (u >> 3) ? (2048 * g + kWRowBytes * kS) : 2048 * g;
+}
 
 // Transpose scratch of the FFTs: two planes (re, im) of 32 x 32 floats,
 // element (r, j) at 33 r + j: rows and columns of a half-wavefront hit 32
@@ -33,10 +60,10 @@ struct Planes {
 };
 static_assert(2 * kS * Planes::kPitch <= kLdsFloats, "planes fit the block's LDS");
 
-// Upper 8 KiB of the block's LDS: one spectrum in bin layout, parked while
-// the matrix-core path transforms the second.
+// One spectrum in bin layout (8 KiB), parked while the matrix-core path,
+// which uses no other LDS, transforms the second.
 __device__ __forceinline__ float2* park(float* lds) {
-    return reinterpret_cast<float2*>(lds + 2 * kS * kS);
+    return reinterpret_cast<float2*>(lds);
 }
 
 // ---------------------------------------------------------------- twiddles

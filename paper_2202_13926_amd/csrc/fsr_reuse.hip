@@ -23,7 +23,7 @@ namespace fsr {
 // blockIdx.y; the host sizes the grid so that every bx lies in [0, nbx).
 // Frame f's image, mask and output start f * frame_stride elements after
 // frame 0's, its argmax log (if any) f * log_stride entries after.
-__global__ __launch_bounds__(64) void fsr_reuse_s32(PlainLaunch p, float delta, int32_t step,
+__global__ __launch_bounds__(64, 4) void fsr_reuse_s32(PlainLaunch p, float delta, int32_t step,
                                                     int32_t by_lo, int32_t slope, int64_t frame_stride,
                                                     int64_t log_stride) {
     __shared__ __align__(16) float lds[kLdsFloats];
