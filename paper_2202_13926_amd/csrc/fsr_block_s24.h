@@ -19,29 +19,29 @@
 //
 // DFT: both real tiles in one complex transform z = (f~ - mu) w + j s w
 // (s a power of two, as in the S = 32 kernel), two radix-3 x 8 passes
-// (s24_pass) with twiddles from the table F[m][k] = exp(-j 2 pi m k / S) in
-// LDS, then split into the two exactly Hermitian spectra.
+// (s24_pass) whose few twiddles each lane takes from the table in global
+// memory, then split into the two exactly Hermitian spectra.
 //
-// LDS per wavefront: the DFT table (S^2 float2) and a scratch area (the
-// passes' 24 x 25 float2, then the spectrum) during the transforms; during the iterations W with its columns repeated once (24
-// rows of 48 entries, entry (R, C) = W[R][C mod S]) at a row pitch of 52
-// entries, 9.75 KiB.  Slot (i, j) of lane (a, b) reads row (a - u + 8 i)
-// mod S, wrapped per row slot i, and column b + 8 j + S - v, which needs no
-// wrap: three row bases per iteration, each with immediate offsets for j.
-// One read covers eight consecutive rows (mod S) of eight consecutive
-// entries; at a pitch of 52 entries (104 words, 40 mod 64) the eight rows
-// start 0, 40, 16, 56, 32, 8, 48, 24 words into the 64 banks, so every bank
-// serves two words, the fewest for 64 lanes of 8 bytes, and every half
-// wavefront (four rows) covers the 32 banks of a half twice.  A pitch of 48
-// (96 words) starts the rows alternately at 0 and 32: 3,072 bank-conflict
-// cycles per block.  Measured on the 1080p frame at I = 100 (before the W
-// reads were issued ahead of the model's lane exchange, which took 2.40 to
-// 2.33-2.37 ms), pitches timed side by side: pitch 52 2.40 ms, 48
-// 2.45-2.47 ms, 50 2.48 ms on one box;
-// 56 (10.5 KiB, fewer resident wavefronts) 2.51 ms against 2.41 ms at 48 on
-// another.  Earlier layouts against 2.40 ms at pitch 48: rows and columns
-// both repeated up to 40 (12.5 KiB, two wraps) 2.57 ms; both repeated in
-// full (48 x 48, 19.5 KiB, a uniform shift) 3.50 ms; the 48-lane layout of
+// LDS per wavefront: a scratch area during the transforms (the passes'
+// 24 x 25 float2, then the spectrum); during the iterations W with its first
+// 16 columns repeated: 24 rows of 40 entries, 7.5 KiB.  Slot (i, j) of lane
+// (a, b) reads row (a - u + 8 i) mod S, wrapped per row slot i, and column
+// (b - v) mod S + 8 j, wrapped once for all j: three row bases per iteration,
+// each with immediate offsets for j.  One read covers eight consecutive rows
+// (mod S) of eight entries; rows start 16 words apart (mod 64), so the four
+// rows of a half wavefront cover the 64 banks once, wherever the columns
+// wrap.
+//
+// The table's size decides: the loop issues in about 230 of the 305 cycles
+// per SIMD and iteration that it took with 16 wavefronts per compute unit.
+// Repeating all columns (pitch 52, which serves every bank twice per half
+// wavefront; 9.75 KiB, 16 wavefronts) against this table (20 wavefronts, four
+// more address instructions): 2.15 against 2.01 ms per 1080p frame at
+// I = 100, of which the set-up 0.314 and 0.275 ms (the DFT table is no longer
+// copied to LDS).  Padded to 12 wavefronts: 2.60 ms.  Earlier layouts,
+// against 2.40 ms for the first with every lane busy: rows and columns both
+// repeated up to 40 (12.5 KiB, two wraps) 2.57 ms; both repeated in full
+// (48 x 48, 19.5 KiB, a uniform shift) 3.50 ms; the 48-lane layout of
 // fsr_block_sg.h 3.27 ms.
 #pragma once
 
@@ -50,13 +50,14 @@
 
 namespace fsr {
 
+typedef float f32x9 __attribute__((ext_vector_type(9)));
+
 struct S24 {
     static constexpr int S = 24;
     static constexpr int NS = 9;                  // slots per lane
-    static constexpr int kPitch = 52;             // W table: S rows of 2S entries (float2), this pitch
-    static constexpr int kTabFloats = 2 * S * S;  // DFT table, then scratch
+    static constexpr int kPitch = 40;             // W table: S rows of S + 16 entries (float2)
     static constexpr int kLdsFloats = 2 * S * kPitch;
-    static_assert(kTabFloats + 2 * 24 * 25 <= kLdsFloats, "transforms fit in the W table's space");
+    static_assert(2 * 24 * 25 <= kLdsFloats, "transforms fit in the W table's space");
     static constexpr int kArgmaxPairs = 1024;     // 576 (key, lane) pairs, padded to 2^10
 };
 
@@ -81,6 +82,20 @@ __device__ __forceinline__ void s24_codes(int a, int b, uint32_t (&code)[S24::NS
     *map_hi = (uint32_t)(m >> 32);
 }
 
+// A lane's twiddles of one pass, for the element index p it holds: W24^p,
+// W24^2p, and W8^k2 of its outputs k = p + 8 q, q = 0..2, from row F[1] of the
+// DFT table in global memory (LDS is what limits the resident wavefronts).
+struct S24Twiddles {
+    float re[5], im[5];
+    __device__ __forceinline__ S24Twiddles(const float2* dft, int p) {
+        constexpr int S = S24::S;
+        table_entry(dft, S + p, re[0], im[0]);
+        table_entry(dft, S + 2 * p, re[1], im[1]);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) table_entry(dft, S + 3 * ((p + 8 * q) / 3), re[2 + q], im[2 + q]);
+    }
+};
+
 // One 24-point DFT pass over the 24 sequences of one axis, radix 3 x 8:
 // with element x = p + 8 q (p < 8 across lanes, q < 3 in the lane's slots)
 // and output k = k1 + 3 k2 (k1 < 3, k2 < 8),
@@ -91,14 +106,13 @@ __device__ __forceinline__ void s24_codes(int a, int b, uint32_t (&code)[S24::NS
 // Horner's rule in W8^k2, which keeps the natural layout (output k = p + 8 q
 // in the slot of element p + 8 q).  kAlongM: along m (p = a, q = i, the
 // sequence n = b + 8 j), else along n (p = b, q = j, the sequence
-// k = a + 8 i).  ftab is the DFT table, row F[1] = W24^q.
+// k = a + 8 i).
 template <bool kAlongM>
-__device__ __forceinline__ void s24_pass(float (&re)[S24::NS], float (&im)[S24::NS], const float2* ftab,
+__device__ __forceinline__ void s24_pass(float (&re)[S24::NS], float (&im)[S24::NS], const S24Twiddles& tw,
                                          float2* buf, int a, int b) {
-    constexpr int S = S24::S, P = 25;
+    constexpr int P = 25;
     constexpr float kH3 = 0.866025403784438647f;   // sin(pi / 3)
     const int p = kAlongM ? a : b, o = kAlongM ? b : a;
-    const float2 t1 = ftab[S + p], t2 = ftab[S + 2 * p];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         const int s0 = kAlongM ? r : 3 * r, ds = kAlongM ? 3 : 1;   // slot of q = 0, step per q
@@ -108,8 +122,8 @@ __device__ __forceinline__ void s24_pass(float (&re)[S24::NS], float (&im)[S24::
         const float hr = fmaf(-0.5f, tr, x0r), hi = fmaf(-0.5f, ti, x0i);
         float y1r = fmaf(kH3, di, hr), y1i = fmaf(-kH3, dr, hi);    // x0 + W3 x1 + W3^2 x2
         float y2r = fmaf(-kH3, di, hr), y2i = fmaf(kH3, dr, hi);    // x0 + W3^2 x1 + W3 x2
-        cmul(y1r, y1i, t1.x, t1.y);
-        cmul(y2r, y2i, t2.x, t2.y);
+        cmul(y1r, y1i, tw.re[0], tw.im[0]);
+        cmul(y2r, y2i, tw.re[1], tw.im[1]);
         const int col = o + 8 * r;
         buf[p * P + col] = make_float2(x0r + tr, x0i + ti);
         buf[(8 + p) * P + col] = make_float2(y1r, y1i);
@@ -118,8 +132,7 @@ __device__ __forceinline__ void s24_pass(float (&re)[S24::NS], float (&im)[S24::
     wave_sync();
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        const int k = p + 8 * q, k1 = k % 3, k2 = k / 3;
-        const float2 w = ftab[S + 3 * k2];   // W8^k2
+        const int k1 = (p + 8 * q) % 3;
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const float2* col = buf + 8 * k1 * P + o + 8 * r;
@@ -127,7 +140,7 @@ __device__ __forceinline__ void s24_pass(float (&re)[S24::NS], float (&im)[S24::
 #pragma unroll
             for (int pp = 6; pp >= 0; --pp) {
                 const float2 v = col[pp * P];
-                cmul(xr, xi, w.x, w.y);
+                cmul(xr, xi, tw.re[2 + q], tw.im[2 + q]);   // W8^k2
                 xr += v.x;
                 xi += v.y;
             }
@@ -161,15 +174,7 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
     }
     const int a = lane >> 3, b = lane & 7;
     const int y0 = jb.by * B - L, x0 = jb.bx * B - L;
-    float2* ftab = reinterpret_cast<float2*>(lds);
-    float2* scr = reinterpret_cast<float2*>(lds + S24::kTabFloats);
-
-    // ---- DFT table into LDS (the same for every block)
-    {
-        const global_t<const uint64_t>* src = global_ptr(reinterpret_cast<const uint64_t*>(tab.dft_sg));
-        uint64_t* dst = reinterpret_cast<uint64_t*>(ftab);
-        for (int i = lane; i < S * S; i += 64) dst[i] = src[i];
-    }
+    float2* scr = reinterpret_cast<float2*>(lds);
 
     // ---- gather and weighting: slot s holds pixel (a + 8 i, b + 8 j)
     float xr[NS], wr[NS];
@@ -196,8 +201,6 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
     const int tm = L + ti, tn = L + tj;
     float acc = 0.0f;
     const int iters = jb.iterations;
-    wave_sync();   // DFT table written
-
     if (any_known != 0) {
         // ---- R_w = mu W + DFT2((f~ - mu) w), mu the weighted mean of the
         // known support pixels, as in the other block routines
@@ -227,8 +230,8 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
             zr[s] = xr[s];
             zi[s] = wr[s] * sc;
         }
-        s24_pass<true>(zr, zi, ftab, scr, a, b);    // along m: C[k][n]
-        s24_pass<false>(zr, zi, ftab, scr, a, b);   // along n: Z[k][l]
+        s24_pass<true>(zr, zi, S24Twiddles(tab.dft_sg, a), scr, a, b);    // along m: C[k][n]
+        s24_pass<false>(zr, zi, S24Twiddles(tab.dft_sg, b), scr, a, b);   // along n: Z[k][l]
 #pragma unroll
         for (int s = 0; s < NS; ++s) scr[(a + 8 * (s / 3)) * S + b + 8 * (s % 3)] = make_float2(zr[s], zi[s]);
         wave_sync();
@@ -264,10 +267,10 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
         float wf[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) wf[s] = global_ptr(tab.freq_w)[(a + 8 * (s / 3)) * S + b + 8 * (s % 3)];
-        // lane i of tw_re / tw_im holds F[1][i mod S], read before the W
-        // table overwrites the DFT table
-        const float2 tw = ftab[S + (lane % S)];
-        const int tw_re = __float_as_int(tw.x), tw_im = __float_as_int(tw.y);
+        // lane i of tw_re / tw_im holds F[1][i mod S]
+        float twx, twy;
+        table_entry(tab.dft_sg, S + (lane % S), twx, twy);
+        const int tw_re = opaque(__float_as_int(twx)), tw_im = opaque(__float_as_int(twy));
         uint32_t code[NS], map_lo, map_hi;
         s24_codes(a, b, code, &map_lo, &map_hi);
         // the loads of the loop's constants complete here, not at their first
@@ -275,21 +278,30 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
 #pragma unroll
         for (int s = 0; s < NS; ++s) wf[s] = __int_as_float(opaque(__float_as_int(wf[s])));
         wave_sync();   // every lane has read the spectrum and the table
-        // W, rows and columns duplicated
+        // W, columns 0 .. 15 repeated
         float2* wtab = reinterpret_cast<float2*>(lds);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int k = a + 8 * (s / 3), l = b + 8 * (s % 3);
             const float2 wv = make_float2(wr[s], wi[s]);
             wtab[k * P + l] = wv;
-            wtab[k * P + l + S] = wv;
+            if (s % 3 < 2) wtab[k * P + l + S] = wv;   // columns 0 .. 15 again
         }
         // lane constants kept as computed here
-        // the lane's byte offset 8 P a + 8 b of entry (a, b)
-        const int ab8 = opaque(8 * P * a + 8 * b);
+        // byte offsets of the lane's row a and column b
+        const int a8 = opaque(8 * P * a), b8 = opaque(8 * b);
         const int tmn = opaque(tm | (tn << 16));
         const char* wbytes = reinterpret_cast<const char*>(wtab);
         wave_sync();
+
+        // the residual spectrum as two 9-wide vectors (contiguous register
+        // tuples) during the loop, for the indexed read of the winning bin
+        f32x9 vr, vi;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            vr[s] = xr[s];
+            vi[s] = xi[s];
+        }
 
         // the loop comes in two copies, with and without the argmax log, so
         // that the one without carries no per-iteration branch for it
@@ -300,7 +312,7 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
                 uint32_t key[NS];
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
-                    const float e = fmaf(xr[s], xr[s], xi[s] * xi[s]);
+                    const float e = fmaf(vr[s], vr[s], vi[s] * vi[s]);
                     key[s] = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | code[s];
                 }
                 uint32_t mx;
@@ -342,8 +354,8 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
                                       (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)map_hi, ln) << 32;
                 const int slot = (int)((wmap >> (4 * cw)) & 15u);
                 const int u = (ln >> 3) + 8 * (slot / 3), v = (ln & 7) + 8 * (slot % 3);
-                const float pr = readlane_f(xr[slot], ln);
-                const float pim = readlane_f(xi[slot], ln);
+                const float pr = readlane_f(vr[slot], ln);
+                const float pim = readlane_f(vi[slot], ln);
                 const float cr = gi * pr, ci = gi * pim;    // gamma * p (Eqs. 10-11)
                 if constexpr (decltype(with_log)::value) {
                     if (lane == 0) jb.log[it] = (uint16_t)(u * S + v);
@@ -351,13 +363,14 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
 
                 // residual (Eqs. 12, 14-15): bin (k, l) = (a + 8 i, b + 8 j) reads
                 // W[(k - u) mod S][(l - v) mod S], table entry
-                // ((a - u + 8 i) mod S, b + 8 j + S - v).  Byte offset 8 P x + y
-                // of row x, with the column part y = 8 (b + S - v) in [8, 8 P):
-                // a row below 0 or at S and above is wrapped by a minimum of
-                // unsigned values (x itself when in range, else x +/- S rows;
-                // out of range the other one is negative, i.e. huge unsigned)
-                const int uv8 = __builtin_amdgcn_readfirstlane(8 * (S - v) - 8 * P * u);   // scalar
-                const uint32_t y0 = (uint32_t)(ab8 + uv8);
+                // ((a - u + 8 i) mod S, (b - v) mod S + 8 j).  Byte offset
+                // 8 P x + y of row x, with the column part y in [0, 8 P): a
+                // value below 0 or at S (rows, or columns) and above is
+                // wrapped by a minimum of unsigned values (itself when in
+                // range, else itself +/- S; out of range the other one is
+                // negative, i.e. huge unsigned)
+                const uint32_t col = (uint32_t)(b8 - 8 * v);
+                const uint32_t y0 = (uint32_t)(a8 - 8 * P * u) + umin(col, col + 8 * S);
                 const uint32_t ad0 = umin(y0, y0 + 8 * P * S);
                 const uint32_t r1a = ad0 + 64 * P, r2a = ad0 + 128 * P;
                 const uint32_t ad1 = umin(r1a, r1a - 8 * P * S);
@@ -380,10 +393,10 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
 
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
-                    xr[s] = fmaf(-cr, w[s].x, xr[s]);
-                    xr[s] = fmaf(ci, w[s].y, xr[s]);
-                    xi[s] = fmaf(-cr, w[s].y, xi[s]);
-                    xi[s] = fmaf(-ci, w[s].x, xi[s]);
+                    vr[s] = fmaf(-cr, w[s].x, vr[s]);
+                    vr[s] = fmaf(ci, w[s].y, vr[s]);
+                    vi[s] = fmaf(-cr, w[s].y, vi[s]);
+                    vi[s] = fmaf(-ci, w[s].x, vi[s]);
                 }
             }
         };
