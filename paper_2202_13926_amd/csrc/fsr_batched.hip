@@ -139,8 +139,7 @@ __device__ __forceinline__ BlockJob batch_job(const BatchLaunch& p, int64_t g, i
     jb.height = d.height;
     jb.width = d.width;
     jb.stride = d.stride;
-    jb.by = (int32_t)(local / d.nbx);
-    jb.bx = (int32_t)(local % d.nbx);
+    set_position(jb, (uint32_t)local, d.nbx);
     jb.iterations = d.iterations;
     return jb;
 }

@@ -178,26 +178,13 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
 
     // ---- gather and weighting: slot s holds pixel (a + 8 i, b + 8 j)
     float xr[NS], wr[NS];
-    uint64_t any_known = 0;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int m = a + 8 * (s / 3), n = b + 8 * (s % 3);
-        const int y = y0 + m, x = x0 + n;
-        const bool in = (unsigned)y < (unsigned)jb.height && (unsigned)x < (unsigned)jb.width;
-        const int64_t off = in ? (int64_t)y * jb.stride + x : 0;
-        const uint8_t kraw = jb.mask[off];
-        const float fraw = jb.image[off];
-        const float rp = global_ptr(tab.rho_pow)[m * S + n];
-        const uint8_t k = in ? kraw : (uint8_t)0;
-        any_known |= ballot(k != 0);
-        xr[s] = k ? fraw : 0.0f;
-        wr[s] = k ? rp : 0.0f;
-    }
+    const uint64_t any_known = gather_support<S>(jb, y0, x0, a, b, [](int s) { return 8 * (s / 3); },
+                                                 [](int s) { return 8 * (s % 3); }, tab.rho_pow, xr, wr);
 
     // ---- target pixel owned by this lane (lanes 0 .. B*B-1; the other
     // lanes model pixel (L, L) and discard it)
     const bool owner = lane < B * B;
-    const int ti = owner ? lane / B : 0, tj = owner ? lane - (lane / B) * B : 0;
+    const int ti = owner ? lane_div(lane, B) : 0, tj = owner ? lane - ti * B : 0;
     const int tm = L + ti, tn = L + tj;
     float acc = 0.0f;
     const int iters = jb.iterations;

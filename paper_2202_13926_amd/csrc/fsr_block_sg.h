@@ -258,27 +258,14 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
 
     // ---- gather and weighting: slot s holds pixel (G s + h, c)
     float xr[NS], wr[NS];
-    uint64_t any_known = 0;
-    const int x = x0 + c;
-    const bool xin = active && (unsigned)x < (unsigned)jb.width;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int m = G * s + h, y = y0 + m;
-        const bool in = xin && (unsigned)y < (unsigned)jb.height;
-        const int64_t off = in ? (int64_t)y * jb.stride + x : 0;
-        const uint8_t kraw = jb.mask[off];
-        const float fraw = jb.image[off];
-        const float rp = global_ptr(tab.rho_pow)[m * S + c];
-        const uint8_t k = in ? kraw : (uint8_t)0;
-        any_known |= ballot(k != 0);
-        xr[s] = k ? fraw : 0.0f;
-        wr[s] = k ? rp : 0.0f;
-    }
+    static_assert(NL == 64, "every lane holds pixels");
+    const uint64_t any_known = gather_support<S>(jb, y0, x0, h, c, [](int s) { return G * s; },
+                                                 [](int) { return 0; }, tab.rho_pow, xr, wr);
 
     // ---- target pixel owned by this lane (lanes 0 .. B*B-1; the other
     // lanes model pixel (L, L) and discard it)
     const bool owner = lane < B * B;
-    const int ti = owner ? lane / B : 0, tj = owner ? lane - (lane / B) * B : 0;
+    const int ti = owner ? lane_div(lane, B) : 0, tj = owner ? lane - ti * B : 0;
     const int tm = L + ti, tn = L + tj;
     float acc = 0.0f;
     const int iters = jb.iterations;

@@ -102,7 +102,7 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
     const int lane = (int)(threadIdx.x & 63);
     const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wavefront of the block
     const int c = lane & 31, h = lane >> 5;
-    const int ti = lane / B, tj = lane - (lane / B) * B;
+    const int ti = lane_div(lane, B), tj = lane - ti * B;
     const int tm = L + ti, tn = L + tj;
 
     // ---- gather and weighting, pixel (m, n) = (2s + h, c) of slots

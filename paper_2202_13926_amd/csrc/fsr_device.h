@@ -322,6 +322,22 @@ __device__ __forceinline__ float readlane_f(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// lane / B for a block edge B in 1..8: a multiplication (B is a run-time
+// value, and the compiler's division is some twenty instructions).
+constexpr uint32_t kDivMagic[9] = {0, 65536, 32769, 21846, 16385, 13108, 10923, 9363, 8193};
+
+constexpr bool div_magic_exact() {
+    for (uint32_t b = 1; b <= 8; ++b)
+        for (uint32_t l = 0; l < 64; ++l)
+            if ((l * kDivMagic[b]) >> 16 != l / b) return false;
+    return true;
+}
+static_assert(div_magic_exact(), "lane / B by multiplication must be exact");
+
+__device__ __forceinline__ int lane_div(int lane, int B) {
+    return (int)(((uint32_t)lane * kDivMagic[B]) >> 16);
+}
+
 // Workgroup index -> block index so that each of the 8 XCDs (which take
 // workgroups round-robin) walks one contiguous range of blocks and its L2
 // sees the overlapping supports of neighbouring blocks.
