@@ -108,53 +108,49 @@ __device__ __forceinline__ void negate(const bf16x8 (&a)[kTerms], bf16x8 (&n)[kT
 __device__ __forceinline__ void dft2_real_mfma(float (&xr)[16], float (&xi)[16], const bf16x8* fop_in,
                                                int lane) {
     const int c = lane & 31, h = lane >> 5;
-    // loaded anew by every call (they hit the cache): keeping them live
-    // from one transform to the next would cost registers
-    const bf16x8* fop = opaque_ptr(fop_in);
-    bf16x8 f[2][2][kTerms];
+    // Loaded anew for every K-step (they hit the cache): all twelve operands
+    // at once take 48 registers, and kept from one pass to the next they put
+    // the kernel at 146 registers, three wavefronts per SIMD
+    const auto operands = [&](int part, int q, bf16x8 (&f)[kTerms]) {
+        const bf16x8* fop = opaque_ptr(fop_in);
 #pragma unroll
-    for (int part = 0; part < 2; ++part)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int i = 0; i < kTerms; ++i)
-                f[part][q][i] = global_ptr(fop)[((part * 2 + q) * kMfmaMaxTerms + i) * 64 + lane];
-    bf16x8 x[2][kTerms];
-    split8(xr, x[0]);
-    split8(xr + 8, x[1]);
+        for (int i = 0; i < kTerms; ++i)
+            f[i] = global_ptr(fop)[((part * 2 + q) * kMfmaMaxTerms + i) * 64 + lane];
+    };
 
     // pass 1: C_part^T[n][k] = sum_m x[m][n] F_part[m][k]; accumulator r of
     // lane (c, h) holds C_part[k = c][n = 8 (r / 4) + 4 h + r % 4]
-    f32x16 cp[2];
+    f32x16 cp[2] = {};
 #pragma unroll
-    for (int part = 0; part < 2; ++part) {
-        f32x16 acc = {};
+    for (int q = 0; q < 2; ++q) {
+        bf16x8 x[kTerms], f[2][kTerms];
+        operands(0, q, f[0]);
+        operands(1, q, f[1]);
+        split8(xr + 8 * q, x);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) acc = mfma_split(x[q], f[part][q], acc);
-        cp[part] = acc;
+        for (int part = 0; part < 2; ++part) cp[part] = mfma_split(x, f[part], cp[part]);
     }
 
     // pass 2: accumulators 8 q .. 8 q + 7 are the A operand of K-step q:
     // Y_re = C_re Re F - C_im Im F,  Y_im = C_re Im F + C_im Re F
-    bf16x8 a[2][2][kTerms];
-#pragma unroll
-    for (int part = 0; part < 2; ++part)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = cp[part][8 * q + j];
-            split8(v, a[part][q]);
-        }
     f32x16 yr = {}, yi = {};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        bf16x8 na[kTerms];
-        negate(a[1][q], na);
-        yr = mfma_split(a[0][q], f[0][q], yr);
-        yi = mfma_split(a[0][q], f[1][q], yi);
-        yr = mfma_split(na, f[1][q], yr);
-        yi = mfma_split(a[1][q], f[0][q], yi);
+        bf16x8 a[2][kTerms], na[kTerms], f[2][kTerms];
+        operands(0, q, f[0]);
+        operands(1, q, f[1]);
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = cp[part][8 * q + j];
+            split8(v, a[part]);
+        }
+        negate(a[1], na);
+        yr = mfma_split(a[0], f[0], yr);
+        yi = mfma_split(a[0], f[1], yi);
+        yr = mfma_split(na, f[1], yr);
+        yi = mfma_split(a[1], f[0], yi);
     }
 
     // accumulator r = 4 g + i of lane (c, h) holds Y[k = 8 g + 4 h + i][l = c].
