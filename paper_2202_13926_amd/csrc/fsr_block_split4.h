@@ -21,11 +21,15 @@
 // fsr_block.h (kDftFft32), so the result is bitwise that of the
 // one-wavefront routine.
 //
-// Measured (64 x 64 frame, 256 blocks, I = 100): 41.2 us a call against 47.8
-// with one wavefront per block (322 against 393 ns an iteration) and 43.8
-// with the two-stage reduction; eight wavefronts per block 44.5.  A step of
-// the sequential variant at VGA: 23.4 us at I = 50 against 29.2 before, of
-// which the set-up (I = 0) 4.8 against 8.7 us.
+// Measured (64 x 64 frame, 256 blocks, I = 100): 40.1 us a call against 47.8
+// with one wavefront per block (310 against 393 ns an iteration); two-stage
+// reduction 43.8; eight wavefronts per block 44.5.  What is left of an
+// iteration is mostly three LDS round trips (keys out, keys in, W and R_w)
+// and the six steps of the reduction; a lone wavefront also pays some 4.5
+// cycles for every instruction, scalar ones included, hence the iterations in
+// pairs (constant buffers) and the addresses taken from the bin index.  A
+// step of the sequential variant at VGA, I = 0: 4.7 us against 8.7 with the
+// set-up on one wavefront.
 #pragma once
 
 #include "fsr_block.h"
@@ -54,7 +58,7 @@ struct SplitLds {
         float2 tile[kSlots * 64];   // (f~, w) of slot s, lane
     };
     float2 ex[16 * 64];
-    float2 r[2][kSlots][64];
+    float2 r[2][kBins];
     uint32_t key[2][kSplitWaves][64];
     int known[kSplitWaves];
 };
@@ -108,6 +112,12 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
     // ---- gather and weighting, pixel (m, n) = (2s + h, c) of slots
     // 4q .. 4q + 3; all loads go out together (an address that holds nothing
     // of use reads pixel 0)
+    // the target pixel of the lane: written at the end, loaded here
+    const int ty = jb.by * B + ti, tx = jb.bx * B + tj;
+    const bool writes = q == 0 && lane < B * B && ty < jb.height && tx < jb.width;
+    const int64_t toff = writes ? (int64_t)ty * jb.stride + tx : 0;
+    const uint8_t tknown = jb.mask[toff];
+    const float tvalue = jb.image[toff];
     {
         const int y0 = jb.by * B - L, x0 = jb.bx * B - L;
         const int x = x0 + c;
@@ -232,9 +242,11 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
 
         // R_w of this wavefront's slots, for the wavefronts that need the winner's
 #pragma unroll
-        for (int s = 0; s < NS; ++s) sh.r[0][NS * q + s][lane] = make_float2(vr[s], vi[s]);
-        for (int it = 0; it < iters; ++it) {
-            const int buf = it & 1;
+        for (int s = 0; s < NS; ++s) sh.r[0][64 * (NS * q + s) + lane] = make_float2(vr[s], vi[s]);
+
+        // one iteration on buffer kBuf; returns the bin
+        const auto iterate = [&](auto buffer) {
+            constexpr int kBuf = decltype(buffer)::value;
             // this wavefront's largest key of each lane (Eq. 16, the same keys
             // as the one-wavefront routine)
             uint32_t lmax = 0;
@@ -244,22 +256,24 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
                 const uint32_t key = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | (code0 - (uint32_t)s);
                 lmax = umax(lmax, key);
             }
-            sh.key[buf][q][lane] = lmax;
+            sh.key[kBuf][q][lane] = lmax;
             __syncthreads();
             // every wavefront reduces all keys: over the wavefronts, then the
             // lanes; equal keys go to the lower lane
 #pragma unroll
-            for (int w = 0; w < kSplitWaves; ++w) lmax = umax(lmax, sh.key[buf][w][lane]);
+            for (int w = 0; w < kSplitWaves; ++w) lmax = umax(lmax, sh.key[kBuf][w][lane]);
             const uint32_t mx = wave_max_u32(lmax);
             const int ln = (int)__builtin_ctzll(ballot(lmax == mx));
-            const int slot = 15 - (int)(mx & 15u);
-            const int idx = 64 * slot + ln;
-            const int u = idx >> 5, v = idx & 31;
-            const float2 rw = sh.r[buf][slot][ln];
+            const int idx = 64 * (15 - (int)(mx & 15u)) + ln;   // 32 u + v
+            // A lone wavefront pays for every scalar instruction too, so the
+            // addresses come from 8 idx = 256 u + 8 v and the phase from idx
+            // itself (32 u n vanishes mod 32)
+            const int idx8 = 8 * idx;
+            const float2 rw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(sh.r[kBuf]) + idx8);
             // residual (Eqs. 12, 14-15) on this wavefront's slots, as in
             // fsr_block.h.  The reads go out first; the model's lane exchange
             // is used after the update
-            const int woff = sub_low_byte(hc8 + (8192 - 256 * u), 8 * v);
+            const int woff = sub_low_byte(hc8 + 8192 - (idx8 & ~255), idx8);
             const float2* wrow = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(sh.w) + woff);
             float2 w[NS];
 #pragma unroll
@@ -268,7 +282,7 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target;
             // every wavefront computes it (no branch in the loop's chain),
             // wavefront 0's is the one written
-            const int q4 = dot2_u16(u | (v << 16), tmn4);
+            const int q4 = dot2_u16((idx >> 5) | (idx << 16), tmn4);
             const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_re));
             const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_im));
             const float cr = gi * rw.x, ci = gi * rw.y;    // gamma * p (Eqs. 10-11)
@@ -278,26 +292,37 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
                 vr[s] = fmaf(ci, w[s].y, vr[s]);
                 vi[s] = fmaf(-cr, w[s].y, vi[s]);
                 vi[s] = fmaf(-ci, w[s].x, vi[s]);
-                sh.r[buf ^ 1][NS * q + s][lane] = make_float2(vr[s], vi[s]);
+                sh.r[kBuf ^ 1][64 * (NS * q + s) + lane] = make_float2(vr[s], vi[s]);
             }
             __builtin_amdgcn_sched_barrier(0);
             acc = fmaf(cr, er, acc);
             acc = fmaf(ci, ei, acc);
-            if (q == 0 && jb.log != nullptr && lane == 0) jb.log[it] = (uint16_t)idx;
-        }
+            return idx;
+        };
+        constexpr std::integral_constant<int, 0> first{};
+        constexpr std::integral_constant<int, 1> second{};
+        // pairs of iterations, in two copies, with and without the log
+        const auto run = [&](auto with_log) {
+            const auto logged = [&](int it, int idx) {
+                if constexpr (decltype(with_log)::value) {
+                    if (q == 0 && lane == 0) jb.log[it] = (uint16_t)idx;
+                }
+            };
+            int it = 0;
+            for (; it + 1 < iters; it += 2) {
+                logged(it, iterate(first));
+                logged(it + 1, iterate(second));
+            }
+            if (it < iters) logged(it, iterate(first));
+        };
+        if (jb.log != nullptr) run(std::true_type{});
+        else run(std::false_type{});
     } else if (q == 0 && jb.log != nullptr) {
         for (int it = lane; it < iters; it += 64) jb.log[it] = (uint16_t)0xFFFF;
     }
 
     // ---- compose (Sec. II): known pixels copied, unknown pixels Re g
-    if (q == 0 && lane < B * B) {
-        const int y = jb.by * B + ti, xx = jb.bx * B + tj;
-        if (y < jb.height && xx < jb.width) {
-            const int64_t off = (int64_t)y * jb.stride + xx;
-            const uint8_t k = jb.mask[off];
-            jb.out[off] = k ? jb.image[off] : acc;
-        }
-    }
+    if (writes) jb.out[toff] = tknown ? tvalue : acc;
 }
 
 }  // namespace fsr
