@@ -504,7 +504,7 @@ static fsr_status reuse_call(fsr_context* ctx, const float* image, const uint8_t
     if ((st = context_tables(ctx, S, params->rho, &p.tab, cap == hipStreamCaptureStatusNone)) != FSR_OK)
         return st;
     hipError_t e = launch_reuse(p, reuse_weight, n_frames, n_frames > 1 ? frame_stride : 0,
-                                (hipStream_t)stream);
+                                cap == hipStreamCaptureStatusNone, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "launch of the reuse-variant kernels");
     return FSR_OK;
 }

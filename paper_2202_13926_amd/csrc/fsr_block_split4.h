@@ -98,7 +98,9 @@ __device__ __forceinline__ void split_dft32_pass(float (&re)[4], float (&im)[4],
     }
 }
 
-// kReuse: as in fsr_block.h.
+// kReuse: as in fsr_block.h; outputs are stored, and reused pixels loaded, by
+// agent-scope accesses (another workgroup of the same launch may read, or
+// have written, them).
 template <bool kReuse>
 __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int B, int L, float gamma,
                                                         const BlockTables& tab, SplitLds& sh) {
@@ -135,7 +137,8 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             rp[j] = global_ptr(tab.rho_pow)[m * kS + c];
             if constexpr (kReuse) {
                 earlier[j] = in[j] && (m < L || (m < L + B && c < L));
-                old[j] = jb.out[earlier[j] ? off : 0];
+                old[j] = __hip_atomic_load(jb.out + (earlier[j] ? off : 0), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         uint64_t any = 0;
@@ -322,7 +325,11 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
     }
 
     // ---- compose (Sec. II): known pixels copied, unknown pixels Re g
-    if (writes) jb.out[toff] = tknown ? tvalue : acc;
+    if (writes) {
+        const float value = tknown ? tvalue : acc;
+        if constexpr (kReuse) __hip_atomic_store(jb.out + toff, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else jb.out[toff] = value;
+    }
 }
 
 }  // namespace fsr
