@@ -407,6 +407,7 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
                 // Objectives that agree to 2^-19 relative tie, and ties go to the
                 // smaller slot, then (below) to the lower lane: the smaller bin.
                 int idx;
+                uint64_t won = 0;   // lanes of the largest key
                 if constexpr (kArgmax == kArgmaxWave) {
                     uint32_t lmax = 0;
 #pragma unroll
@@ -416,7 +417,8 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
                         lmax = umax(lmax, key);
                     }
                     const uint32_t mx = wave_max_u32(lmax);
-                    const int ln = (int)__builtin_ctzll(ballot(lmax == mx));
+                    won = ballot(lmax == mx);
+                    const int ln = (int)__builtin_ctzll(won);
                     idx = 64 * (15 - (int)(mx & 15u)) + ln;
                 } else {
 #pragma unroll
@@ -444,10 +446,11 @@ __device__ __forceinline__ void reconstruct_block(const BlockJob& jb, int B, int
                     }
                     idx = __builtin_amdgcn_readfirstlane((int)argmax_lds[0].y);
                     wave_sync();   // the next iteration overwrites the pairs
+                    won = uint64_t(1) << (idx & 63);
                 }
-                const int slot = idx >> 6, ln = idx & 63;
-                const float pr = readlane_f(vr[slot], ln);
-                const float pim = readlane_f(vi[slot], ln);
+                const int slot = idx >> 6;
+                float pr, pim;
+                read_lowest(won, vr[slot], vi[slot], pr, pim);
                 const int u = idx >> 5, v = idx & 31;
                 const float cr = gi * pr, ci = gi * pim;    // gamma * p (Eqs. 10-11)
                 if constexpr (decltype(with_log)::value) {

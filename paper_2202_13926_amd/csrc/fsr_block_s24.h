@@ -304,12 +304,14 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
                 }
                 uint32_t mx;
                 int ln;
+                uint64_t won = 0;   // lanes of the largest key
                 if constexpr (kArgmax == kArgmaxWave) {
                     uint32_t lmax = 0;
 #pragma unroll
                     for (int s = 0; s < NS; ++s) lmax = umax(lmax, key[s]);
                     mx = wave_max_u32(lmax);
-                    ln = (int)__builtin_ctzll(ballot(lmax == mx));
+                    won = ballot(lmax == mx);
+                    ln = (int)__builtin_ctzll(won);
                 } else {
 #pragma unroll
                     for (int s = 0; s < NS; ++s) argmax_lds[64 * s + lane] = make_uint2(key[s], (uint32_t)lane);
@@ -334,15 +336,17 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
                     mx = (uint32_t)__builtin_amdgcn_readfirstlane((int)argmax_lds[0].x);
                     ln = __builtin_amdgcn_readfirstlane((int)argmax_lds[0].y);
                     wave_sync();   // the next iteration overwrites the pairs
+                    won = uint64_t(1) << ln;
                 }
                 // the winner's slot from its code, through the winning lane's map
                 const int cw = (int)(mx & 15u);
-                const uint64_t wmap = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)map_lo, ln) |
-                                      (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)map_hi, ln) << 32;
+                float wlo, whi;
+                read_lowest(won, __uint_as_float(map_lo), __uint_as_float(map_hi), wlo, whi);
+                const uint64_t wmap = (uint64_t)__float_as_uint(wlo) | (uint64_t)__float_as_uint(whi) << 32;
                 const int slot = (int)((wmap >> (4 * cw)) & 15u);
                 const int u = (ln >> 3) + 8 * (slot / 3), v = (ln & 7) + 8 * (slot % 3);
-                const float pr = readlane_f(vr[slot], ln);
-                const float pim = readlane_f(vi[slot], ln);
+                float pr, pim;
+                read_lowest(won, vr[slot], vi[slot], pr, pim);
                 const float cr = gi * pr, ci = gi * pim;    // gamma * p (Eqs. 10-11)
                 if constexpr (decltype(with_log)::value) {
                     if (lane == 0) jb.log[it] = (uint16_t)(u * S + v);

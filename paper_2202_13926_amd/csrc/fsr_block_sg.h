@@ -394,6 +394,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                 // objective key (Eq. 16), as in the S = 32 kernel: float32 bits
                 // with the 4 low mantissa bits replaced by 15 - slot
                 int slot, ln;
+                uint64_t won = 0;   // lanes of the largest key
                 if constexpr (kArgmax == kArgmaxWave) {
                     uint32_t lmax = 0;
 #pragma unroll
@@ -404,7 +405,8 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                     }
                     if (!active) lmax = 0;   // real keys carry a slot code >= 4
                     const uint32_t mx = wave_max_u32(lmax);
-                    ln = (int)__builtin_ctzll(ballot(lmax == mx));
+                    won = ballot(lmax == mx);
+                    ln = (int)__builtin_ctzll(won);
                     slot = 15 - (int)(mx & 15u);
                 } else {
                     constexpr int kPairs = sg_argmax_pairs<S>();
@@ -435,6 +437,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                     wave_sync();   // the next iteration overwrites the pairs
                     slot = pos >> 6;
                     ln = pos & 63;
+                    won = uint64_t(1) << ln;
                 }
                 const int u = G * slot + ln / S, v = ln % S;
                 const int idx = u * S + v;
@@ -446,10 +449,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                 if constexpr (NS <= 4) {
 #pragma unroll
                     for (int s = 0; s < NS; ++s) {
-                        if (slot == s) {
-                            pr = readlane_f(xr[s], ln);
-                            pim = readlane_f(xi[s], ln);
-                        }
+                        if (slot == s) read_lowest(won, xr[s], xi[s], pr, pim);
                     }
                 } else {
                     pr = readlane_f(xr[slot], ln);

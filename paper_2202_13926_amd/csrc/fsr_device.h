@@ -338,6 +338,24 @@ __device__ __forceinline__ int lane_div(int lane, int B) {
     return (int)(((uint32_t)lane * kDivMagic[B]) >> 16);
 }
 
+// Values of a and b in the lowest lane of `lanes` (a ballot, not 0), wave-
+// uniform: two reads of the first active lane with the other lanes switched
+// off.  A read of a lane given by a scalar takes 8.7 cycles of a SIMD against
+// 4.7 (measured at four wavefronts per SIMD), and waits for the lane's number.
+// 1080p frame, I = 100: S = 16 886 -> 862 us, S = 24 2000 -> 1929, S = 32
+// 2748 -> 2719.
+__device__ __forceinline__ void read_lowest(uint64_t lanes, float a, float b, float& ra, float& rb) {
+    uint64_t all;
+    asm("s_and_saveexec_b64 %2, %3\n\t"
+        "v_readfirstlane_b32 %0, %4\n\t"
+        "v_readfirstlane_b32 %1, %5\n\t"
+        "s_mov_b64 exec, %2\n\t"
+        "s_nop 1"   // a vector instruction may read the results next
+        : "=&s"(ra), "=&s"(rb), "=&s"(all)
+        : "s"(lanes), "v"(a), "v"(b)
+        : "scc");
+}
+
 // Workgroup index -> block index so that each of the 8 XCDs (which take
 // workgroups round-robin) walks one contiguous range of blocks and its L2
 // sees the overlapping supports of neighbouring blocks.
