@@ -58,8 +58,14 @@ struct MultiShape {
     // same output, 0.33 against 0.34 ms for the 1080p frame at I = 100
     static constexpr int kScratchPitch = kBlockScratch + 8;
     static constexpr int kWFloats = NB * 4 * S * S;          // W per block, 2S x S float2
-    static constexpr int kLdsFloats = kTabFloats + NB * kScratchPitch > kWFloats
-                                          ? kTabFloats + NB * kScratchPitch : kWFloats;
+    static constexpr int kLoopFloats = kTabFloats + NB * kScratchPitch > kWFloats
+                                           ? kTabFloats + NB * kScratchPitch : kWFloats;
+    // the twiddles of the target model follow; 10 KiB in all, 16 wavefronts
+    // per compute unit.  The 8.06 KiB used would allow 19: us for a 1200 x 1200
+    // frame at I = 200, by wavefronts 12 414, 16 353, 17 and 18 403, 19 and 20 376
+    // (whole numbers of wavefronts per SIMD, and the LDS pipe is shared)
+    static constexpr int kLdsFloats = 2560;
+    static_assert(kLoopFloats + 2 * S <= kLdsFloats, "tables and twiddles fit");
 };
 
 // Maximum and sum over the 8 lanes of this lane's block; every lane of the
@@ -83,10 +89,10 @@ __device__ __forceinline__ float block_sum_f32(float v) {
     return v;
 }
 
-// a * b + c on the full-rate 24-bit multiplier, all per-lane values below 2^24
-__device__ __forceinline__ int mad_u24_lanes(int a, int b, int c) {
+// u a + v b as dot2_u16, with per-lane u | v << 16
+__device__ __forceinline__ int dot2_u16_lanes(int uv, int ab) {
     int r;
-    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    asm("v_dot2_u32_u16 %0, %1, %2, 0" : "=v"(r) : "v"(uv), "v"(ab));
     return r;
 }
 
@@ -247,15 +253,14 @@ __device__ __forceinline__ void reconstruct_multi(const MultiJob& im, int B, int
 
     // ---- target pixels of this lane
     float acc[T];
-    int tm4[T], tn4[T];
+    int tmn8[T];
     bool own[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int px = c + S * t;
         own[t] = px < B * B;
         const int ti = own[t] ? px / B : 0, tj = own[t] ? px - (px / B) * B : 0;
-        tm4[t] = opaque(4 * (L + ti));
-        tn4[t] = opaque(4 * (L + tj));
+        tmn8[t] = opaque((8 * (L + ti)) | ((8 * (L + tj)) << 16));
         acc[t] = 0.0f;
     }
     const int iters = im.iterations;
@@ -301,10 +306,9 @@ __device__ __forceinline__ void reconstruct_multi(const MultiJob& im, int B, int
     float wf[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) wf[s] = global_ptr(tab.freq_w)[s * S + c];
-    // lane c of each block holds F[1][c] = exp(-j 2 pi c / S), read before W
-    // overwrites the table
-    const float2 tw = ftab[S + c];
-    const int tw_re = __float_as_int(tw.x), tw_im = __float_as_int(tw.y);
+    // F[1][q] = exp(-j 2 pi q / S), kept for the loop beyond the W table
+    float2* twt = reinterpret_cast<float2*>(lds + Sh::kLoopFloats);
+    if (lane < S) twt[lane] = ftab[S + lane];
     // the loads of the loop's constants complete here, not at their first
     // use inside the loop (which would put their waits in the loop body)
 #pragma unroll
@@ -351,12 +355,15 @@ __device__ __forceinline__ void reconstruct_multi(const MultiJob& im, int B, int
                 if (logp != nullptr && c == 0) logp[it] = has_known ? (uint16_t)(u * S + v) : (uint16_t)0xFFFF;
             }
 
-            // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target
+            // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target, the
+            // twiddle read as one table entry (four lane exchanges fewer per
+            // iteration: 1200 x 1200 frame at I = 200 390 -> 375 us)
+            const int uv = u | (v << 16);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int q4 = mad_u24_lanes(u, tm4[t], mad_u24_lanes(v, tn4[t], 0)) & (4 * S - 1);
-                const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(first4 + q4, tw_re));
-                const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(first4 + q4, tw_im));
+                const int q8 = dot2_u16_lanes(uv, tmn8[t]) & (8 * S - 8);
+                const float2 e2 = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(twt) + q8);
+                const float er = e2.x, ei = e2.y;
                 acc[t] = fmaf(cr, er, acc[t]);
                 acc[t] = fmaf(ci, ei, acc[t]);
             }
