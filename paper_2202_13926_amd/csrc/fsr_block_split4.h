@@ -21,15 +21,19 @@
 // fsr_block.h (kDftFft32), so the result is bitwise that of the
 // one-wavefront routine.
 //
-// Measured (64 x 64 frame, 256 blocks, I = 100): 40.1 us a call against 47.8
-// with one wavefront per block (310 against 393 ns an iteration); two-stage
-// reduction 43.8; eight wavefronts per block 44.5.  What is left of an
-// iteration is mostly three LDS round trips (keys out, keys in, W and R_w)
-// and the six steps of the reduction; a lone wavefront also pays some 4.5
-// cycles for every instruction, scalar ones included, hence the iterations in
-// pairs (constant buffers) and the addresses taken from the bin index.  A
-// step of the sequential variant at VGA, I = 0: 4.7 us against 8.7 with the
-// set-up on one wavefront.
+// Measured (64 x 64 frame, 256 blocks, I = 100): 36.2 us a call against 47.1
+// with one wavefront per block (270 against 385 ns an iteration).  What is
+// left of an iteration is mostly three LDS round trips (keys out, keys in, W
+// and R_w) and the six steps of the reduction; a lone wavefront also pays some
+// 4.5 cycles for every instruction, scalar ones included, and waits out each
+// result that the next instruction needs.  Hence the iterations in pairs
+// (constant buffers), the addresses taken from the bin index, and the
+// objective step by step over the slots with the model's twiddle from a table
+// in LDS: these two took the call from 40.5 to 36.2 us, and the VGA frame of
+// the sequential variant from 30.0 to 26.5 ms.  Before them, with a two-stage
+// reduction 43.8 us instead of 42.2, with eight wavefronts per block 44.5.
+// Keys by lane (one 16-byte read each) 37.3.  A step of the sequential variant
+// at VGA, I = 0: 4.1 us against 6.4 with one wavefront per block.
 #pragma once
 
 #include "fsr_block.h"
@@ -41,10 +45,11 @@ constexpr int kSplitWaves = 4;
 constexpr int kSplitSlots = kSlots / kSplitWaves;   // slots per wavefront
 
 // Calls (or steps) of at most this many blocks, two per compute unit, take
-// this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 576
-// blocks: here 41.2 / 45.6 / 46.2 / 55.5, one wavefront per block 47.8 / 48.4 /
-// 48.5 / 48.7 (a third workgroup on a compute unit costs more than the
-// latency it saves: every wavefront repeats the reduction).
+// this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 528 /
+// 768 / 1024 blocks: here 36.3 / 40.6 / 41.2 / 47.7 / 48.0 / 73.7, one
+// wavefront per block 47.1 / 47.5 / 47.9 / 47.9 / 47.7 / 48.0 (a third
+// workgroup on a compute unit costs what the latency saves: every wavefront
+// repeats the reduction).
 constexpr int64_t kSplitMaxBlocks = 512;
 
 // LDS of a workgroup: the W table with its rows repeated (row r at r and
@@ -58,6 +63,7 @@ struct SplitLds {
         float2 tile[kSlots * 64];   // (f~, w) of slot s, lane
     };
     float2 ex[16 * 64];
+    float2 tw[kS];   // exp(-j 2 pi i / 32), read by the model
     float2 r[2][kBins];
     uint32_t key[2][kSplitWaves][64];
     int known[kSplitWaves];
@@ -233,8 +239,8 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             sh.w[k * kS + c] = make_float2(wr, wi);
             sh.w[(k + kS) * kS + c] = make_float2(wr, wi);
         }
-        const int tw_re = __float_as_int(kTw.re[c]), tw_im = __float_as_int(kTw.im[c]);
-        const int tmn4 = opaque((4 * tm) | ((4 * tn) << 16));
+        if (q == 0 && h == 0) sh.tw[c] = make_float2(kTw.re[c], kTw.im[c]);
+        const int tmn8 = opaque((8 * tm) | ((8 * tn) << 16));
         // byte offset of the lane's entry (h, c) in W, plus this wavefront's
         // first slot (512 bytes per slot): the low byte stays 8 c
         const int hc8 = opaque(256 * h + 8 * c + 512 * NS * q);
@@ -252,11 +258,22 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             constexpr int kBuf = decltype(buffer)::value;
             // this wavefront's largest key of each lane (Eq. 16, the same keys
             // as the one-wavefront routine)
+            // -- step by step over the slots, so that no instruction waits
+            // for the one before it
+            float e[NS];
             uint32_t lmax = 0;
 #pragma unroll
+            for (int s = 0; s < NS; ++s) e[s] = vi[s] * vi[s];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) e[s] = fmaf(vr[s], vr[s], e[s]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) e[s] *= wf[s];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const float e = fmaf(vr[s], vr[s], vi[s] * vi[s]);
-                const uint32_t key = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | (code0 - (uint32_t)s);
+                const uint32_t key = (__float_as_uint(e[s]) & 0xFFFFFFF0u) | (code0 - (uint32_t)s);
                 lmax = umax(lmax, key);
             }
             sh.key[kBuf][q][lane] = lmax;
@@ -285,9 +302,8 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target;
             // every wavefront computes it (no branch in the loop's chain),
             // wavefront 0's is the one written
-            const int q4 = dot2_u16((idx >> 5) | (idx << 16), tmn4);
-            const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_re));
-            const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_im));
+            const int q8 = dot2_u16((idx >> 5) | (idx << 16), tmn8) & (8 * kS - 8);
+            const float2 tw = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(sh.tw) + q8);
             const float cr = gi * rw.x, ci = gi * rw.y;    // gamma * p (Eqs. 10-11)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
@@ -298,8 +314,8 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
                 sh.r[kBuf ^ 1][64 * (NS * q + s) + lane] = make_float2(vr[s], vi[s]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            acc = fmaf(cr, er, acc);
-            acc = fmaf(ci, ei, acc);
+            acc = fmaf(cr, tw.x, acc);
+            acc = fmaf(ci, tw.y, acc);
             return idx;
         };
         constexpr std::integral_constant<int, 0> first{};
