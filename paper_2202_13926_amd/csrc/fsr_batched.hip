@@ -171,7 +171,7 @@ template <int kWaves, int S, int kDft>
 __device__ __forceinline__ void grid_body(const BatchLaunch& p, float* lds) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t groups = (p.total_blocks + kWaves - 1) / kWaves;
-    const int64_t g = xcd_contiguous(blockIdx.x, groups) * kWaves + wave;
+    const int64_t g = xcd_runs(blockIdx.x, groups) * kWaves + wave;
     if (g >= p.total_blocks) return;
     int img = 0;
     int64_t img_begin = 0, img_end = 0;
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(64 * kWaves) void fsr_batched_grid_multi(BatchLaunc
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t units = p.total_blocks / kUnit;
     const int64_t groups = (units + kWaves - 1) / kWaves;
-    const int64_t unit = xcd_contiguous(blockIdx.x, groups) * kWaves + wave;
+    const int64_t unit = xcd_runs(blockIdx.x, groups) * kWaves + wave;
     if (unit >= units) return;
     const int64_t g = unit * kUnit;
     int img = 0;

@@ -252,15 +252,8 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
-// a * b + c on the 24-bit multiplier (full rate), a wave-uniform.  The
-// compiler otherwise widens small products to the quarter-rate 32/64-bit
-// multiply-add.
-__device__ __forceinline__ int mad_u24(int a, int b, int c) {
-    int r;
-    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "s"(a), "v"(b), "v"(c));
-    return r;
-}
-
+// a * b on the 24-bit multiplier (full rate).  The compiler otherwise widens
+// small products to the quarter-rate 32/64-bit multiply-add.
 __device__ __forceinline__ int mul_u24(int a, int b) {
     int r;
     asm("v_mul_u32_u24 %0, %1, %2" : "=v"(r) : "s"(a), "v"(b));
@@ -356,13 +349,27 @@ __device__ __forceinline__ void read_lowest(uint64_t lanes, float a, float b, fl
         : "scc");
 }
 
-// Workgroup index -> block index so that each of the 8 XCDs (which take
-// workgroups round-robin) walks one contiguous range of blocks and its L2
-// sees the overlapping supports of neighbouring blocks.
-__device__ __forceinline__ int64_t xcd_contiguous(int64_t wg, int64_t n) {
-    const int64_t per = n / 8, rem = n % 8;
+// Workgroup index -> block index, so that each of the 8 XCDs (which take
+// workgroups round-robin, each at its own pace) walks runs of kXcdRun
+// consecutive blocks, whose overlapping supports its L2 then sees, and the
+// XCDs walk the index space side by side.  With one contiguous eighth of the
+// space per XCD, work that is uneven along the space was uneven between the
+// XCDs: in a batch, whose images are ordered by their iterations, the XCD with
+// the most took 1.7 times the average (24 images, S = 32: 1044 against 617 us;
+// 8 images, S = 16: 4194 against 2426), and so did an image with a part in
+// which nothing is known (1080p with its lower half lost, S = 32: 2669 against
+// 1433).  By run length, for those two batches: 1 block
+// 627 / 2487, 8 616 / 2423, 32 617 / 2426, 128 619 / 2428, 512 638 / 2442; a
+// 1080p frame alone takes the same time with each (S = 16, 24 and 32).
+constexpr int64_t kXcdRun = 32;
+
+__device__ __forceinline__ int64_t xcd_runs(int64_t wg, int64_t n) {
+    constexpr int64_t kStripe = 8 * kXcdRun;
     const int64_t x = wg % 8, j = wg / 8;
-    return x * per + (x < rem ? x : rem) + j;
+    const int64_t full = n / kStripe * kStripe;   // whole stripes, then the rest in eighths
+    if (wg < full) return j / kXcdRun * kStripe + x * kXcdRun + j % kXcdRun;
+    const int64_t per = (n - full) / 8, rem = (n - full) % 8;
+    return full + x * per + (x < rem ? x : rem) + (j - full / 8);
 }
 
 }  // namespace fsr

@@ -8,7 +8,7 @@ namespace fsr {
 template <int kDft, int kArgmax>
 __global__ __launch_bounds__(64, kDft == kDftSplitBf16 ? 4 : 2) void fsr_plain_s32(PlainLaunch p) {
     __shared__ __align__(16) float lds[kLdsFloats + (kArgmax == kArgmaxLds ? kArgmaxLdsFloats : 0)];
-    const int64_t blk = xcd_contiguous(blockIdx.x, p.n_blocks);
+    const int64_t blk = xcd_runs(blockIdx.x, p.n_blocks);
     reconstruct_block<kDft, kArgmax, false>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, lds,
                                      reinterpret_cast<uint2*>(lds + kLdsFloats));
 }
@@ -16,7 +16,7 @@ __global__ __launch_bounds__(64, kDft == kDftSplitBf16 ? 4 : 2) void fsr_plain_s
 // The same with kSplitWaves wavefronts per block (fsr_block_split4.h).
 __global__ __launch_bounds__(64 * kSplitWaves) void fsr_plain_split_s32(PlainLaunch p) {
     __shared__ __align__(16) SplitLds sh;
-    const int64_t blk = xcd_contiguous(blockIdx.x, p.n_blocks);
+    const int64_t blk = xcd_runs(blockIdx.x, p.n_blocks);
     reconstruct_block_split<false>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, sh);
 }
 

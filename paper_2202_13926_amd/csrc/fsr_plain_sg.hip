@@ -13,7 +13,7 @@ template <int S, int kArgmax = kArgmaxWave>
 __global__ __launch_bounds__(64) void fsr_plain_sg(PlainLaunch p) {
     constexpr int kExtra = kArgmax == kArgmaxLds ? 2 * sg_argmax_pairs<S>() : 0;
     __shared__ __align__(16) float lds[SgShape<S>::kLdsFloats + kExtra];
-    const int64_t blk = xcd_contiguous(blockIdx.x, p.n_blocks);
+    const int64_t blk = xcd_runs(blockIdx.x, p.n_blocks);
     reconstruct_block_sg<S, false, kArgmax>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, lds,
                                             reinterpret_cast<uint2*>(lds + SgShape<S>::kLdsFloats));
 }
@@ -22,7 +22,7 @@ template <int kArgmax = kArgmaxWave>
 __global__ __launch_bounds__(64) void fsr_plain_s24(PlainLaunch p) {
     constexpr int kExtra = kArgmax == kArgmaxLds ? 2 * S24::kArgmaxPairs : 0;
     __shared__ __align__(16) float lds[S24::kLdsFloats + kExtra];
-    const int64_t blk = xcd_contiguous(blockIdx.x, p.n_blocks);
+    const int64_t blk = xcd_runs(blockIdx.x, p.n_blocks);
     reconstruct_block_s24<false, kArgmax>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, lds,
                                           reinterpret_cast<uint2*>(lds + S24::kLdsFloats));
 }
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(64) void fsr_plain_multi(PlainLaunch p) {
     jb.stride = im.stride;
     jb.iterations = im.iterations;
     jb.nbx = im.nbx;
-    jb.first_block = xcd_contiguous(blockIdx.x, waves) * NB;
+    jb.first_block = xcd_runs(blockIdx.x, waves) * NB;
     jb.n_blocks = p.n_blocks;
     reconstruct_multi<S, T>(jb, p.block, p.border, p.gamma, p.tab, lds);
 }
