@@ -27,6 +27,7 @@ size_t workspace_bytes_for(int32_t n) {
 // What the schedule choice needs to know about a planned batch.
 struct PlanTotals {
     int64_t total_blocks = 0;
+    int32_t unit = 1;             // blocks per wavefront
     double work = 0.0;            // sum over images of blocks x iterations
     int32_t max_iterations = 0;
 };
@@ -79,10 +80,13 @@ struct QueueOrder {
 fsr_status fill_table(const fsr_image_desc* descs, int32_t n, const fsr_params* params, const int32_t* order,
                       const int64_t* blocks, DevDesc* table, PlanTotals* tot) {
     const int B = params->block;
+    *tot = PlanTotals{};
+    int64_t sum = 0;
+    for (int32_t j = 0; j < n; ++j) sum += blocks[j];
     // blocks per wavefront: each image's range in the index space is padded
     // to a multiple of it, so that no wavefront spans two images
-    const int64_t unit = batch_unit(params->block + 2 * params->border, B);
-    *tot = PlanTotals{};
+    tot->unit = blocks_per_wave(params->block + 2 * params->border, B, sum);
+    const int64_t unit = tot->unit;
     int64_t begin = 0;
     for (int32_t j = 0; j < n; ++j) {
         const fsr_image_desc& d = descs[order[j]];
@@ -176,7 +180,7 @@ fsr_status finish_prepare(fsr_context* ctx, int32_t n, const fsr_params* params,
     prep->launch.block = params->block;
     prep->launch.border = params->border;
     prep->launch.support = S;
-    prep->launch.unit = batch_unit(S, params->block);
+    prep->launch.unit = plan.unit;
     prep->launch.gamma = params->gamma;
     prep->launch.dft = params->dft == FSR_DFT_SPLIT_BF16 ? 1 : 0;
     if (schedule) {

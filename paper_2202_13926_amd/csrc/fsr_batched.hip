@@ -4,10 +4,10 @@
 // a plain grid: fsr_batched_grid_s32) or run persistently, popping `chunk`
 // consecutive blocks at a time from a global counter until the index space
 // is exhausted (fsr_batched_s32).  Supports 8, 16 and 24 have the same two
-// forms (fsr_batched_grid_sg, fsr_batched_sg); at S = 8 with B <= 4 a
-// wavefront takes units of eight blocks of one image (fsr_batched_grid_multi,
-// fsr_batched_multi), every image's block range then being padded to a
-// multiple of eight.  Each block runs the same arithmetic as in the one-image
+// forms (fsr_batched_grid_sg, fsr_batched_sg); at S = 8 with B <= 4 and more
+// than a few thousand blocks (blocks_per_wave) a wavefront takes units of
+// eight blocks of one image (fsr_batched_grid_multi, fsr_batched_multi), every
+// image's block range then being padded to a multiple of eight.  Each block runs the same arithmetic as in the one-image
 // kernel, so its result does not depend on the batch it is part of.
 #include "fsr_batch_internal.h"
 #include "fsr_block.h"
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * kWaves) void fsr_batched_sg(BatchLaunch p) {
     queue_body<kWaves, S, kDftFft32>(p, lds);
 }
 
-// ---- S = 8, B <= 4: units of eight blocks of one image
+// ---- units of eight blocks of one image (blocks_per_wave)
 __device__ __forceinline__ MultiJob batch_multi_job(const BatchLaunch& p, int64_t g, int img) {
     const DevDesc& d = p.descs[img];
     MultiJob jb;

@@ -39,6 +39,21 @@ struct ImageDesc {
     int64_t block_begin;    // first global block id of this image (batched path)
 };
 
+// Blocks per wavefront of a call (or batch) of n_blocks blocks at these
+// parameters: 8 at S = 8 with B <= 4 (fsr_block_multi.h), else 1, and 1 for
+// calls whose blocks all find a wavefront slot of their own: eighteen
+// wavefronts on each of the 256 compute units.  Such a call is bound by the
+// latency of an iteration, which is longer when each lane holds eight bins.
+// Measured at I = 100, us a call with 1 and 8 blocks per wavefront: 256 blocks
+// 18.7 and 35.5, 2025 21.5 and 35.7, 4096 27.7 and 36.2, 5184 34.8 and 36.5,
+// 8100 41.9 and 37.1; with B = 2, 256 blocks 18.6 and 32.2, 4096 27.8 and 33.4,
+// 5184 34.8 and 33.3.
+constexpr int64_t kOnePerWaveMaxBlocks = 18 * 256;
+
+inline int32_t blocks_per_wave(int32_t support, int32_t block, int64_t n_blocks) {
+    return support == 8 && block * block <= 16 && n_blocks > kOnePerWaveMaxBlocks ? 8 : 1;
+}
+
 struct PlainLaunch {
     ImageDesc img;
     int32_t block, border;  // B, L

@@ -1,7 +1,8 @@
 // fsr_plain_sg.hip -- one-image FSR at supports 8, 16 and 24: one workgroup
 // of one wavefront per block (fsr_block_sg.h; at S = 24 fsr_block_s24.h), or
-// at S = 8 with B <= 4 eight blocks per wavefront (fsr_block_multi.h; bitwise
-// the result of the one-block routine).
+// at S = 8 with B <= 4 and more than a few thousand blocks eight blocks per
+// wavefront (blocks_per_wave; fsr_block_multi.h, bitwise the result of the
+// one-block routine).
 #include "fsr_block.h"
 #include "fsr_block_multi.h"
 #include "fsr_block_s24.h"
@@ -69,9 +70,8 @@ hipError_t launch_plain_sg(const PlainLaunch& p, hipStream_t stream) {
         }
         return hipGetLastError();
     }
-    const int bb = p.block * p.block;   // target pixels per block
-    if (p.support == 8 && bb <= 8) return launch_multi<8, 1>(p, stream);
-    if (p.support == 8 && bb <= 16) return launch_multi<8, 2>(p, stream);
+    if (blocks_per_wave(p.support, p.block, p.n_blocks) == 8)
+        return p.block * p.block <= 8 ? launch_multi<8, 1>(p, stream) : launch_multi<8, 2>(p, stream);
     const dim3 grid((unsigned)p.n_blocks), block(64);
     switch (p.support) {
     case 8: hipLaunchKernelGGL(fsr_plain_sg<8>, grid, block, 0, stream, p); break;
