@@ -36,6 +36,10 @@ struct BatchLaunch {
     int32_t unit;           // blocks per wavefront (blocks_per_wave): 1 or 8;
                             // every image's block range is a multiple of it,
                             // and chunk counts units
+    // a launch of part of one image (n_images = 1): its blocks from
+    // first_block on, of which those from end_block on are padding
+    int64_t first_block = 0;
+    int64_t end_block = INT64_MAX;
 };
 
 // Launches the queue reset (when chunk > 0) and the batched kernel with

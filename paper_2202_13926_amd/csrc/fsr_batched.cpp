@@ -277,11 +277,19 @@ void release_batch_state(BatchState& st) {
 fsr_status batched_enqueue(fsr_context* ctx, const fsr_image_desc* descs, int32_t n,
                            const fsr_params* params, const fsr_batch_schedule* schedule,
                            void* workspace, size_t ws_bytes, hipStream_t stream,
-                           StagingSlot* slot, std::mutex* slot_mutex) {
+                           StagingSlot* slot, std::mutex* slot_mutex, BlockRange range) {
     BatchPlan plan;
     Prepared prep;
     fsr_status st = prepare(ctx, descs, n, params, schedule, workspace, ws_bytes, &plan, &prep);
     if (st != FSR_OK) return st;
+    if (n == 1) {
+        const int64_t unit = prep.launch.unit;
+        const int64_t blocks = fsr_num_blocks(descs[0].height, descs[0].width, params->block);
+        const int64_t end = std::min(range.end, blocks), first = std::min(range.first, end);
+        prep.launch.first_block = first;
+        prep.launch.end_block = end;
+        prep.launch.total_blocks = plan.totals.total_blocks = (end - first + unit - 1) / unit * unit;
+    }
     if (plan.totals.total_blocks == 0) return FSR_OK;
     DeviceGuard g(context_device(ctx));
     if (g.error() != hipSuccess) return hip_fail(g.error(), "hipSetDevice");

@@ -130,7 +130,7 @@ __device__ __forceinline__ void locate(const BatchLaunch& p, int64_t g, int& img
 
 __device__ __forceinline__ BlockJob batch_job(const BatchLaunch& p, int64_t g, int img) {
     const DevDesc& d = p.descs[img];
-    const int64_t local = g - d.block_begin;
+    const int64_t local = g - d.block_begin + p.first_block;
     BlockJob jb;
     jb.image = global_ptr(d.image);
     jb.mask = global_ptr(d.mask);
@@ -244,8 +244,9 @@ __device__ __forceinline__ MultiJob batch_multi_job(const BatchLaunch& p, int64_
     jb.stride = d.stride;
     jb.iterations = d.iterations;
     jb.nbx = d.nbx;
-    jb.first_block = g - d.block_begin;
+    jb.first_block = g - d.block_begin + p.first_block;
     jb.n_blocks = (int64_t)((d.height + p.block - 1) / p.block) * d.nbx;
+    if (jb.n_blocks > p.end_block) jb.n_blocks = p.end_block;
     return jb;
 }
 

@@ -50,14 +50,19 @@ struct BatchState {
 
 void release_batch_state(BatchState& st);
 
+// Blocks [first, end) of an image, in raster order.
+struct BlockRange {
+    int64_t first = 0, end = INT64_MAX;
+};
+
 // Validates a batch and enqueues descriptor upload (through `slot`, under
 // `slot_mutex` when given) plus the batched kernel on `stream`.  Nothing is
 // touched before validation passes.  Shared by fsr_reconstruct_batched and
-// the server.
+// the server, which may have only `range` of a single image reconstructed.
 fsr_status batched_enqueue(fsr_context* ctx, const fsr_image_desc* descs, int32_t n,
                            const fsr_params* params, const fsr_batch_schedule* schedule,
                            void* workspace, size_t ws_bytes, hipStream_t stream,
-                           StagingSlot* slot, std::mutex* slot_mutex);
+                           StagingSlot* slot, std::mutex* slot_mutex, BlockRange range = {});
 
 fsr_status set_error(fsr_status st, const char* msg);
 fsr_status errorf(fsr_status st, const char* fmt, ...);

@@ -47,6 +47,10 @@ struct Request {
     uint8_t* d_mask = nullptr;
     float* d_out = nullptr;
     hipEvent_t uploaded = nullptr;
+    // rows of blocks that need only the image rows copied first, and the event
+    // behind these rows (0: the frame was copied in one piece)
+    int32_t first_rows = 0;
+    hipEvent_t first_uploaded = nullptr;
     double t_submit = 0, t_admit = 0, t_launch = 0, t_done = 0;
 };
 
@@ -143,14 +147,34 @@ const void* device_view(const void* p, int32_t memory) {
 // through the runtime's copy.
 constexpr size_t kKernelUploadMaxBytes = size_t(4) << 20;
 
+// Copies rows [y0, y1) of a host request's image and mask into its arena slot.
+hipError_t copy_rows(const Request& q, int32_t y0, int32_t y1, hipMemcpyKind kind, hipStream_t stream) {
+    const fsr_request& r = q.r;
+    const size_t w = (size_t)r.width, h = (size_t)(y1 - y0), dst = (size_t)y0 * w, src = (size_t)y0 * (size_t)r.stride;
+    const hipError_t e = hipMemcpy2DAsync(q.d_img + dst, w * 4, r.image + src, (size_t)r.stride * 4, w * 4, h, kind, stream);
+    if (e != hipSuccess) return e;
+    return hipMemcpy2DAsync(q.d_mask + dst, w, r.mask + src, (size_t)r.stride, w, h, kind, stream);
+}
+
+// Rows of blocks that are reconstructed while the rest of the frame is still
+// on its way.  A quarter: the device waits for a quarter of the copy instead
+// of all of it, and where the reconstruction takes at least three times as
+// long as the copy, the rest has arrived when the first part ends.
+int32_t first_part_rows(const fsr_request& r, const fsr_params& p) {
+    return std::max(1, (r.height + p.block - 1) / p.block / 4);
+}
+
 // Copies a request's image and mask into its arena slot on `stream`.  A copy
 // command waits for the kernels that other streams are running, so frames
 // that should start beside a running one are moved by a copy kernel: device
 // memory always, pinned host frames up to kKernelUploadMaxBytes.  Larger host
 // frames use the runtime's copy, which moves them faster over PCIe than a
 // kernel's reads and occupies no compute units (measured on the 240 frames/s
-// stream of 720p to 2160p frames: p50 34 against 47 ms).
-bool upload(fsr_server* s, Request& q, hipStream_t stream) {
+// stream of 720p to 2160p frames: p50 34 against 47 ms).  With `in_parts` a
+// large pinned frame is copied in two parts, so that its reconstruction can
+// start behind the first (four frames of VGA to 2160p sent to an idle server,
+// S = 16: 7.2 -> 6.4 ms until the last result is back on the host).
+bool upload(fsr_server* s, Request& q, hipStream_t stream, bool in_parts) {
     const fsr_request& r = q.r;
     const size_t bytes = (size_t)r.height * (size_t)r.width * 5;
     const bool by_kernel = r.memory == FSR_MEM_DEVICE || bytes <= kKernelUploadMaxBytes;
@@ -165,11 +189,18 @@ bool upload(fsr_server* s, Request& q, hipStream_t stream) {
                               (size_t)r.height, stream);
     } else {
         const hipMemcpyKind kind = r.memory == FSR_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-        e = hipMemcpy2DAsync(q.d_img, (size_t)r.width * 4, r.image, (size_t)r.stride * 4,
-                             (size_t)r.width * 4, r.height, kind, stream);
-        if (e == hipSuccess)
-            e = hipMemcpy2DAsync(q.d_mask, (size_t)r.width, r.mask, (size_t)r.stride, (size_t)r.width,
-                                 r.height, kind, stream);
+        const int32_t rows = first_part_rows(r, s->params);
+        // the support of these blocks ends L rows below them
+        const int32_t y = (int32_t)std::min<int64_t>(r.height, (int64_t)rows * s->params.block + s->params.border);
+        if (in_parts && !by_kernel && y < r.height && device_view(r.image, r.memory) && device_view(r.mask, r.memory) &&
+            (q.first_uploaded = take_event(s)) != nullptr) {
+            e = copy_rows(q, 0, y, kind, stream);
+            if (e == hipSuccess) e = hipEventRecord(q.first_uploaded, stream);
+            if (e == hipSuccess) e = copy_rows(q, y, r.height, kind, stream);
+            q.first_rows = rows;
+        } else {
+            e = copy_rows(q, 0, r.height, kind, stream);
+        }
     }
     if (e != hipSuccess) {
         fail_server(s, FSR_ERR_HIP, std::string("request upload: ") + hipGetErrorString(e));
@@ -203,7 +234,7 @@ void admit(fsr_server* s) {
         s->stats.peak_bytes_in_use = std::max(s->stats.peak_bytes_in_use, s->stats.bytes_in_use);
         if (s->cfg.mode == FSR_SERVE_FIFO) {
             // reference loop: upload and one-image reconstruction in stream order
-            if (!upload(s, q, s->streams[0])) return;
+            if (!upload(s, q, s->streams[0], false)) return;
             fsr_params p = s->params;
             p.iterations = q.r.iterations;
             fsr_status st = fsr_reconstruct(s->ctx, q.d_img, q.d_mask, q.d_out, q.r.height, q.r.width,
@@ -228,7 +259,9 @@ void admit(fsr_server* s) {
                 fail_server(s, FSR_ERR_HIP, "event creation failed");
                 return;
             }
-            if (!upload(s, q, s->copy_stream)) return;
+            // in parts only for an idle server: beside a running launch the
+            // copy has time
+            if (!upload(s, q, s->copy_stream, s->inflight.empty() && s->admitted.empty())) return;
             if (hipEventRecord(q.uploaded, s->copy_stream) != hipSuccess) {
                 fail_server(s, FSR_ERR_HIP, "hipEventRecord after upload");
                 return;
@@ -251,10 +284,13 @@ void launch_batches(fsr_server* s) {
         // beside a running batch only a small one (sched::batch_size)
         double running = 0.0;
         for (const Launch& r : s->inflight) running = std::max(running, r.work);
-        const size_t n = sched::batch_size(
+        size_t n = sched::batch_size(
             s->admitted.size(), [&](size_t k) { return request_work(s->reqs[s->admitted[k]].r, s->params); },
             (size_t)s->cfg.max_batch, running);
         if (n == 0) return;   // wait for the running batch
+        // a frame that is copied in parts starts by itself, behind the first
+        const bool in_parts = running <= 0.0 && s->reqs[s->admitted.front()].first_rows > 0;
+        if (in_parts) n = 1;
         std::vector<fsr_image_desc> descs(n);
         Launch l;
         l.stream = si;
@@ -262,18 +298,35 @@ void launch_batches(fsr_server* s) {
             const uint64_t id = s->admitted.front();
             s->admitted.pop_front();
             Request& q = s->reqs[id];
-            if (hipStreamWaitEvent(st, q.uploaded, 0) != hipSuccess) {
-                fail_server(s, FSR_ERR_HIP, "hipStreamWaitEvent");
-                return;
-            }
             descs[k] = fsr_image_desc{q.d_img, q.d_mask, q.d_out, nullptr, q.r.height, q.r.width,
                                       (int64_t)q.r.width, q.r.iterations, 0};
             l.ids.push_back(id);
             l.work += request_work(q.r, s->params);
         }
-        const fsr_batch_schedule flat{1, 0, 10, 0};
-        fsr_status rs = batched_enqueue(s->ctx, descs.data(), (int32_t)n, &s->params, &flat,
-                                        s->workspace[si], s->ws_bytes, st, &s->staging[si], nullptr);
+        const auto enqueue = [&](BlockRange range) {
+            const fsr_batch_schedule flat{1, 0, 10, 0};
+            return batched_enqueue(s->ctx, descs.data(), (int32_t)n, &s->params, &flat, s->workspace[si], s->ws_bytes,
+                                   st, &s->staging[si], nullptr, range);
+        };
+        fsr_status rs = FSR_OK;
+        BlockRange range;
+        const Request& front = s->reqs[l.ids.front()];
+        if (in_parts) {
+            range.end = (int64_t)front.first_rows * ((front.r.width + s->params.block - 1) / s->params.block);
+            if (hipStreamWaitEvent(st, front.first_uploaded, 0) != hipSuccess) {
+                fail_server(s, FSR_ERR_HIP, "hipStreamWaitEvent");
+                return;
+            }
+            rs = enqueue(range);
+            range = BlockRange{range.end, INT64_MAX};
+        }
+        for (const uint64_t id : l.ids) {
+            if (hipStreamWaitEvent(st, s->reqs[id].uploaded, 0) != hipSuccess) {
+                fail_server(s, FSR_ERR_HIP, "hipStreamWaitEvent");
+                return;
+            }
+        }
+        if (rs == FSR_OK) rs = enqueue(range);
         l.done = take_event(s);
         if (rs != FSR_OK || !l.done || hipEventRecord(l.done, st) != hipSuccess) {
             fail_server(s, rs != FSR_OK ? rs : FSR_ERR_HIP, fsr_last_error_message());
@@ -286,7 +339,8 @@ void launch_batches(fsr_server* s) {
             q.state = State::Launched;
             q.t_launch = t;
             give_event(s, q.uploaded);
-            q.uploaded = nullptr;
+            give_event(s, q.first_uploaded);
+            q.uploaded = q.first_uploaded = nullptr;
         }
         s->stream_busy[si] = true;
         ++s->stats.launches;
@@ -356,8 +410,10 @@ void worker_main(fsr_server* s) {
     }
     // launches admitted but never started are discarded at shutdown
     for (uint64_t id : s->admitted) {
-        give_event(s, s->reqs[id].uploaded);
-        s->reqs[id].uploaded = nullptr;
+        Request& q = s->reqs[id];
+        give_event(s, q.uploaded);
+        give_event(s, q.first_uploaded);
+        q.uploaded = q.first_uploaded = nullptr;
     }
     s->admitted.clear();
     s->cv_done.notify_all();
@@ -391,8 +447,10 @@ void free_resources(fsr_server* s) {
         (void)hipStreamSynchronize(s->copy_stream);
         (void)hipStreamDestroy(s->copy_stream);
     }
-    for (auto& kv : s->reqs)
-        if (kv.second.uploaded) s->events.push_back(kv.second.uploaded);
+    for (auto& kv : s->reqs) {
+        give_event(s, kv.second.uploaded);
+        give_event(s, kv.second.first_uploaded);
+    }
     for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
     if (s->arena_base) (void)hipFree(s->arena_base);
 }
