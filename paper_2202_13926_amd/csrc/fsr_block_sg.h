@@ -1,10 +1,9 @@
 // fsr_block_sg.h -- one support block of FSR on one wavefront for the smaller
-// even supports S = 8, 16, 24 (Sec. II; the paper sweeps S over 8..32 in
-// Sec. IV and runs its real-time table at S = 16).
+// supports S = 8 and 16 (Sec. II; the paper sweeps S over 8..32 in Sec. IV and
+// runs its real-time table at S = 16; S = 24 has fsr_block_s24.h).
 //
-// Layout: G = 64 / S lane groups; lane = c + S h (c < S, h < G) is active
-// when lane < G S (all 64 lanes for S = 8 and 16, 48 for S = 24).  Slot s of
-// an active lane holds pixel (m = G s + h, n = c) of the tile, and bin
+// Layout: G = 64 / S lane groups; lane = c + S h (c < S, h < G).  Slot s of
+// a lane holds pixel (m = G s + h, n = c) of the tile, and bin
 // (k = G s + h, l = c) of a spectrum, so the bin index k S + l = s G S + lane
 // orders as (slot, lane), as in the S = 32 kernel.
 //
@@ -42,7 +41,6 @@ template <int S>
 struct SgShape {
     static constexpr int G = 64 / S;          // lane groups
     static constexpr int NS = S / G;          // slots per lane
-    static constexpr int NL = G * S;          // active lanes
     static constexpr bool kFullDup = S <= kFullDupMax;   // columns duplicated too
     static constexpr int P = kFullDup ? 2 * S : S;        // W table pitch, float2
     static constexpr int kLoopFloats = kFullDup ? 8 * S * S : 4 * S * S;
@@ -75,21 +73,18 @@ __device__ __forceinline__ int mod_small(int q) {
 }
 
 // 2D DFT of the real values v (slot s = pixel (G s + h, c)) into (re, im)
-// (slot s = bin (G s + h, c)).  Active lanes only carry data; inactive lanes
-// compute duplicates that the caller discards.  `ftab` is the DFT table in
-// LDS, `scr` the scratch area (the tile, S^2 floats, then over it the
-// first pass, S^2 float2).
+// (slot s = bin (G s + h, c)).  `ftab` is the DFT table in LDS, `scr` the
+// scratch area (the tile, S^2 floats, then over it the first pass, S^2
+// float2).
 template <int S>
 __device__ __forceinline__ void dft2_sg(const float (&v)[SgShape<S>::NS], float (&re)[SgShape<S>::NS],
                                         float (&im)[SgShape<S>::NS], const float2* ftab, float* scr,
-                                        int c, int h, bool active) {
+                                        int c, int h) {
     constexpr int G = SgShape<S>::G, NS = SgShape<S>::NS;
     float* tile = scr;                                // [m][n]
     float2* pass1 = reinterpret_cast<float2*>(scr);   // [k][n], over the tile once it is read
-    if (active) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) tile[(G * s + h) * S + c] = v[s];
-    }
+    for (int s = 0; s < NS; ++s) tile[(G * s + h) * S + c] = v[s];
     wave_sync();
     // pass 1 along m: C[k][n] = sum_m x[m][n] F[m][k], k = G s + h, n = c
     float ar[NS], ai[NS];
@@ -108,10 +103,8 @@ __device__ __forceinline__ void dft2_sg(const float (&v)[SgShape<S>::NS], float 
         }
     }
     wave_sync();   // every lane has read the tile
-    if (active) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) pass1[(G * s + h) * S + c] = make_float2(ar[s], ai[s]);
-    }
+    for (int s = 0; s < NS; ++s) pass1[(G * s + h) * S + c] = make_float2(ar[s], ai[s]);
     wave_sync();
     // pass 2 along n: X[k][l] = sum_n C[k][n] F[n][l], k = G s + h, l = c
     float br[NS], bi[NS];
@@ -233,7 +226,7 @@ template <int S, bool kPersistent = false, int kArgmax = kArgmaxWave>
 __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, int L, float gamma,
                                                      const BlockTables& tab_in, float* lds,
                                                      uint2* argmax_lds = nullptr) {
-    constexpr int G = SgShape<S>::G, NS = SgShape<S>::NS, NL = SgShape<S>::NL;
+    constexpr int G = SgShape<S>::G, NS = SgShape<S>::NS;
     const int lane = kPersistent ? opaque((int)(threadIdx.x & 63)) : (int)(threadIdx.x & 63);
     BlockTables tab = tab_in;
     if constexpr (kPersistent) {
@@ -241,11 +234,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
         tab.freq_w = opaque_ptr(tab_in.freq_w);
         tab.dft_sg = opaque_ptr(tab_in.dft_sg);
     }
-    const bool active = lane < NL;
-    // inactive lanes (S = 24) get an in-range (c, h) so that every LDS
-    // address they form stays inside the tables
-    const int c = active ? lane % S : lane - NL;
-    const int h = active ? lane / S : 0;
+    const int c = lane % S, h = lane / S;
     const int y0 = jb.by * B - L, x0 = jb.bx * B - L;
     float2* ftab = reinterpret_cast<float2*>(lds);
     float* scr = lds + 2 * S * S;
@@ -260,7 +249,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
 
     // ---- gather and weighting: slot s holds pixel (G s + h, c)
     float xr[NS], wr[NS];
-    static_assert(NL == 64, "every lane holds pixels");
+    static_assert(G * S == 64, "every lane holds pixels");
     const uint64_t any_known = gather_support<S>(jb, y0, x0, h, c, [](int s) { return G * s; },
                                                  [](int) { return 0; }, tab.rho_pow, xr, wr);
 
@@ -333,8 +322,8 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
             }
             wave_sync();   // every lane has read the spectrum
         } else {
-            dft2_sg<S>(xr, xr, xi, ftab, scr, c, h, active);
-            dft2_sg<S>(wr, wr, wi, ftab, scr, c, h, active);
+            dft2_sg<S>(xr, xr, xi, ftab, scr, c, h);
+            dft2_sg<S>(wr, wr, wi, ftab, scr, c, h);
         }
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -363,17 +352,15 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
         constexpr int P = SgShape<S>::P;   // table pitch in float2
         constexpr bool kFullDup = SgShape<S>::kFullDup;
         float2* wtab = reinterpret_cast<float2*>(lds);
-        if (active) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int k = G * s + h;
-                const float2 wv = make_float2(wr[s], wi[s]);
-                wtab[k * P + c] = wv;
-                wtab[(k + S) * P + c] = wv;
-                if constexpr (kFullDup) {
-                    wtab[k * P + c + S] = wv;
-                    wtab[(k + S) * P + c + S] = wv;
-                }
+        for (int s = 0; s < NS; ++s) {
+            const int k = G * s + h;
+            const float2 wv = make_float2(wr[s], wi[s]);
+            wtab[k * P + c] = wv;
+            wtab[(k + S) * P + c] = wv;
+            if constexpr (kFullDup) {
+                wtab[k * P + c + S] = wv;
+                wtab[(k + S) * P + c + S] = wv;
             }
         }
         // lane constants kept as computed here (the compiler would otherwise
@@ -403,7 +390,6 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                         const uint32_t key = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | (uint32_t)(15 - s);
                         lmax = umax(lmax, key);
                     }
-                    if (!active) lmax = 0;   // real keys carry a slot code >= 4
                     const uint32_t mx = wave_max_u32(lmax);
                     won = ballot(lmax == mx);
                     ln = (int)__builtin_ctzll(won);
@@ -414,7 +400,7 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                     for (int s = 0; s < NS; ++s) {
                         const float e = fmaf(xr[s], xr[s], xi[s] * xi[s]);
                         const uint32_t key = (__float_as_uint(e * wf[s]) & 0xFFFFFFF0u) | (uint32_t)(15 - s);
-                        argmax_lds[64 * s + lane] = make_uint2(active ? key : 0u, (uint32_t)(64 * s + lane));
+                        argmax_lds[64 * s + lane] = make_uint2(key, (uint32_t)(64 * s + lane));
                     }
 #pragma unroll
                     for (int e = 64 * NS; e < kPairs; e += 64) argmax_lds[e + lane] = make_uint2(0u, 0xFFFFFFFFu);
