@@ -165,16 +165,20 @@ FSR_API fsr_status fsr_reconstruct(fsr_context *ctx, const float *image, const u
  *                 0 reuses nothing and gives fsr_reconstruct's result
  *   other arguments as for fsr_reconstruct; `out` is also read: the
  *                 blocks read earlier blocks' reconstructions from it
- * Schedule: with r = ceil(L / B), block (by, bx) runs at wavefront step
- * bx + (r + 1) by, one kernel launch per step; the blocks of a step are
- * independent and every block a block reuses ran at an earlier step.  That
- * is (nbx - 1) + (r + 1)(nby - 1) + 1 launches (1,825 for 1920 x 1080 at
- * B = 4, L = 14), each with at most min(nby, ceil(nbx / (r + 1))) blocks, so
+ * Schedule: with r = ceil(L / B), the blocks that may run side by side are
+ * those of one wavefront step bx + (r + 1) by; a call has
+ * (nbx - 1) + (r + 1)(nby - 1) + 1 steps (1,825 for 1920 x 1080 at B = 4,
+ * L = 14), each of at most min(nby, ceil(nbx / (r + 1))) blocks per frame, so
  * the call is bound by the latency of one block per step rather than by
- * throughput; a step of at most 512 blocks (over all frames) runs each
- * block on four wavefronts, a larger one on one, with bitwise the same
- * result.  S = 32, FSR_DFT_FP32, no flags (FSR_ERR_UNSUPPORTED
- * otherwise); a reuse_weight outside [0, 1] or NaN is FSR_ERR_INVALID_ARG.
+ * throughput.  Where no step has more than 512 blocks (over all frames) the
+ * call is one launch: a workgroup of four wavefronts takes a row of blocks and
+ * waits for the row above by a counter in device memory, which the call takes
+ * from the stream's memory pool and gives back.  Under stream capture, when
+ * that memory cannot be had, or with larger steps, there is one launch per
+ * step, of four wavefronts per block up to 512 blocks and one above.  The
+ * result is bitwise the same.  S = 32, FSR_DFT_FP32, no flags
+ * (FSR_ERR_UNSUPPORTED otherwise); a reuse_weight outside [0, 1] or NaN is
+ * FSR_ERR_INVALID_ARG.
  * Asynchronous on `stream`; capturable into a HIP graph under the same
  * condition as fsr_reconstruct.
  */
@@ -185,9 +189,8 @@ FSR_API fsr_status fsr_reconstruct_reuse(fsr_context *ctx, const float *image, c
 
 /*
  * fsr_reconstruct_reuse over n_frames frames of one size (a video's frames),
- * each reconstructed on its own as above; one launch per wavefront step
- * takes that step's blocks of every frame, which fills the device where one
- * frame's at most min(nby, ceil(nbx / (r + 1))) blocks per step cannot.
+ * each reconstructed on its own as above; a step then has that step's blocks
+ * of every frame, which fills the device where one frame's cannot.
  *   image, mask, out  frame f starts f * frame_stride elements after frame 0;
  *                     rows `stride` elements apart within a frame;
  *                     frame_stride >= (height - 1) * stride + width (frames
@@ -380,7 +383,10 @@ typedef struct fsr_server fsr_server;
  * fetched or released.  Each result is bitwise identical to fsr_reconstruct
  * on the same frame, whatever else shares its launch.  While a batch runs, a
  * second one starts beside it on the other compute stream only if it is at
- * most a quarter of the running batch's work.  The compute streams are
+ * most a quarter of the running batch's work.  A pinned host frame of more
+ * than 4 MiB that reaches an idle server is copied in two parts and launched
+ * by itself, in two launches, the first behind the first part.  The compute
+ * streams are
  * created with a CU mask enabling every compute unit (each then has a
  * hardware queue of its own) and therefore synchronise with the legacy null
  * stream.
