@@ -207,14 +207,20 @@ __device__ __forceinline__ void queue_body(const BatchLaunch& p, float* lds) {
     }
 }
 
+// Four wavefronts per SIMD, as many as the LDS allows, although the split-bf16
+// form would take 136 registers and the persistent ones 145 and 158 (spills of
+// at most 120 bytes outside the iterations).  us for a 1080p frame at I = 100,
+// without and with the bound: split-bf16 grid 3169 and 2994; persistent with
+// chunk 4 and 16 workgroups per compute unit 2954 and 2818, split-bf16 3237 and
+// 3173 (at 10 workgroups per compute unit 3287 and 3296).
 template <int kWaves, int kDft>
-__global__ __launch_bounds__(64 * kWaves) void fsr_batched_grid_s32(BatchLaunch p) {
+__global__ __launch_bounds__(64 * kWaves, 4) void fsr_batched_grid_s32(BatchLaunch p) {
     __shared__ __align__(16) float lds[kWaves * kLdsFloats];
     grid_body<kWaves, kS, kDft>(p, lds);
 }
 
 template <int kWaves, int kDft>
-__global__ __launch_bounds__(64 * kWaves) void fsr_batched_s32(BatchLaunch p) {
+__global__ __launch_bounds__(64 * kWaves, 4) void fsr_batched_s32(BatchLaunch p) {
     __shared__ __align__(16) float lds[kWaves * kLdsFloats];
     queue_body<kWaves, kS, kDft>(p, lds);
 }
