@@ -140,10 +140,18 @@ __global__ __launch_bounds__(64 * kSplitWaves) void fsr_reuse_rows_s32(PlainLaun
 // Rows of a call that the queue takes (4 MiB of counters).
 constexpr int64_t kMaxQueueRows = int64_t(1) << 20;
 
+// At most `widest` rows can make progress at one time; a workgroup that ends
+// its row takes the next.  So the grid holds that many: a workgroup per row
+// would hold LDS and wavefront slots for rows that cannot start yet, on every
+// compute unit where a call has many frames, and keep other streams' kernels
+// out.  us a call with a workgroup per row and with `widest`: 12 frames of
+// 352 x 288, I = 50, 9158 and 8737; 32 of 320 x 240, I = 20, 4404 and 4259
+// (one row per frame more: 8742 and 4528).
+//
 // hipErrorOutOfMemory when the counters cannot be allocated (nothing is
 // enqueued then).
 static hipError_t launch_reuse_rows(const PlainLaunch& p, float delta, int32_t n_frames, int32_t nby, int32_t ahead,
-                                    int64_t frame_stride, int64_t log_stride, hipStream_t stream) {
+                                    int32_t widest, int64_t frame_stride, int64_t log_stride, hipStream_t stream) {
     const int32_t rows = nby * n_frames;
     const int32_t words = (int32_t)(sizeof(RowQueue) / sizeof(int32_t)) + rows;
     void* ws = nullptr;
@@ -155,7 +163,8 @@ static hipError_t launch_reuse_rows(const PlainLaunch& p, float delta, int32_t n
                        static_cast<int32_t*>(ws), words);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(fsr_reuse_rows_s32, dim3(rows), dim3(64 * kSplitWaves), 0, stream, p, delta, n_frames, nby,
+        const int32_t groups = std::min(rows, widest);
+        hipLaunchKernelGGL(fsr_reuse_rows_s32, dim3(groups), dim3(64 * kSplitWaves), 0, stream, p, delta, n_frames, nby,
                            ahead, frame_stride, log_stride, static_cast<RowQueue*>(ws));
         e = hipGetLastError();
     }
@@ -178,8 +187,8 @@ hipError_t launch_reuse(const PlainLaunch& p, float delta, int32_t n_frames, int
     const int64_t log_stride = p.n_blocks * (int64_t)p.img.iterations;
     const int64_t widest = std::min(nby, (nbx + slope - 1) / slope) * n_frames;
     if (may_allocate && widest <= kSplitMaxBlocks && nby * n_frames <= kMaxQueueRows) {
-        const hipError_t e = launch_reuse_rows(p, delta, n_frames, (int32_t)nby, (int32_t)slope, frame_stride,
-                                               log_stride, stream);
+        const hipError_t e = launch_reuse_rows(p, delta, n_frames, (int32_t)nby, (int32_t)slope,
+                                               (int32_t)widest, frame_stride, log_stride, stream);
         if (e != hipErrorOutOfMemory) return e;
     }
     for (int64_t t = 0; t < steps; ++t) {
