@@ -44,8 +44,8 @@ namespace fsr {
 constexpr int kSplitWaves = 4;
 constexpr int kSplitSlots = kSlots / kSplitWaves;   // slots per wavefront
 
-// Calls (or steps) of at most this many blocks, two per compute unit, take
-// this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 528 /
+// Calls (on the null stream, see launch_plain) or steps of at most this many
+// blocks, two per compute unit, take this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 528 /
 // 768 / 1024 blocks: here 36.3 / 40.6 / 41.2 / 47.7 / 48.0 / 73.7, one
 // wavefront per block 47.1 / 47.5 / 47.9 / 47.9 / 47.7 / 48.0 (a third
 // workgroup on a compute unit costs what the latency saves: every wavefront

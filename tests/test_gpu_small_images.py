@@ -64,3 +64,21 @@ def test_same_as_one_wavefront_per_block(ctx, h, w, B, iters, kind):
     assert np.isfinite(got[0]).all()
     assert np.array_equal(got[0], ref[0])
     assert np.array_equal(got[1], ref[1])
+
+
+def test_own_stream_equals_null_stream(ctx):
+    """On a stream of the caller's own a block runs on one wavefront."""
+    print("\n[gpu case] 61x128, null stream against own stream", flush=True)
+    img, mask = frame(61, 128, "half")
+    ti, tm = torch.from_numpy(img).to(DEV), torch.from_numpy(mask).to(DEV)
+    p = fsr.make_params(iterations=45)
+    torch.cuda.synchronize()
+    res = []
+    for stream in (None, torch.cuda.Stream()):
+        out = torch.full_like(ti, float("nan"))
+        log = torch.full((fsr.fsr_num_blocks(61, 128, 4), 45), -1, dtype=torch.int16, device=DEV)
+        torch.cuda.synchronize()
+        fsr.fsr_reconstruct(ctx, ti, tm, out, p, log, stream)
+        torch.cuda.synchronize()
+        res.append((out, log))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
