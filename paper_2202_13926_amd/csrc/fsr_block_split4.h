@@ -1,8 +1,8 @@
-// fsr_block_split4.h -- one S = 32 support block on a workgroup of four
-// wavefronts, for calls that hold too few blocks to fill the device: small
-// images, and the sequential variant (the original FSR that Sec. II departs
-// from), whose blocks depend on one another.  Such a call is bound by the
-// latency of a block, i.e. by the chain of its iterations.
+// fsr_block_split4.h -- one S = 32 support block of the sequential variant
+// (the original FSR that Sec. II departs from) on a workgroup of four
+// wavefronts.  Its blocks depend on one another, so that at one time there
+// are too few to fill the device, and a call is bound by the latency of a
+// block, i.e. by the chain of its iterations.
 //
 // Wavefront q keeps the bins of slots NS q .. NS q + NS - 1 (bins (2s + h, c),
 // NS = 4) in registers and a copy of R_w in LDS; W lies in LDS with every row
@@ -21,15 +21,15 @@
 // fsr_block.h (kDftFft32), so the result is bitwise that of the
 // one-wavefront routine.
 //
-// Measured (64 x 64 frame, 256 blocks, I = 100): 36.2 us a call against 47.1
-// with one wavefront per block (270 against 385 ns an iteration).  What is
+// Measured with a launch of 256 independent blocks at I = 100: 36.2 us against
+// 47.1 with one wavefront per block (270 against 385 ns an iteration).  What is
 // left of an iteration is mostly three LDS round trips (keys out, keys in, W
 // and R_w) and the six steps of the reduction; a lone wavefront also pays some
 // 4.5 cycles for every instruction, scalar ones included, and waits out each
 // result that the next instruction needs.  Hence the iterations in pairs
 // (constant buffers), the addresses taken from the bin index, and the
 // objective step by step over the slots with the model's twiddle from a table
-// in LDS: these two took the call from 40.5 to 36.2 us, and the VGA frame of
+// in LDS: these two took that launch from 40.5 to 36.2 us, and the VGA frame of
 // the sequential variant from 30.0 to 26.5 ms.  Before them, with a two-stage
 // reduction 43.8 us instead of 42.2, with eight wavefronts per block 44.5.
 // Keys by lane (one 16-byte read each) 37.3.  A step of the sequential variant
@@ -44,12 +44,15 @@ namespace fsr {
 constexpr int kSplitWaves = 4;
 constexpr int kSplitSlots = kSlots / kSplitWaves;   // slots per wavefront
 
-// Calls (on the null stream, see launch_plain) or steps of at most this many
-// blocks, two per compute unit, take this routine.  Measured at I = 100, us a call of 256 / 272 / 512 / 528 /
-// 768 / 1024 blocks: here 36.3 / 40.6 / 41.2 / 47.7 / 48.0 / 73.7, one
+// Steps of at most this many blocks, two per compute unit, take this routine.
+// Measured at I = 100, us a launch of 256 / 272 / 512 / 528 / 768 / 1024
+// independent blocks: here 36.3 / 40.6 / 41.2 / 47.7 / 48.0 / 73.7, one
 // wavefront per block 47.1 / 47.5 / 47.9 / 47.9 / 47.7 / 48.0 (a third
 // workgroup on a compute unit costs what the latency saves: every wavefront
-// repeats the reduction).
+// repeats the reduction).  1080p frames (at most 96 blocks per step and frame)
+// in one launch per step, ms a call of 1 / 4 / 5 / 6 / 8 frames: four
+// wavefronts for every step 66.0 / 71.7 / 72.5 / 79.4 / 81.8, one 87.0 / 91.3 /
+// 92.1 / 92.5 / 90.2, four up to this line 66.0 / 71.7 / 72.5 / 83.4 / 83.3.
 constexpr int64_t kSplitMaxBlocks = 512;
 
 // LDS of a workgroup: the W table with its rows repeated (row r at r and
@@ -104,10 +107,8 @@ __device__ __forceinline__ void split_dft32_pass(float (&re)[4], float (&im)[4],
     }
 }
 
-// kReuse: as in fsr_block.h; outputs are stored, and reused pixels loaded, by
-// agent-scope accesses (another workgroup of the same launch may read, or
-// have written, them).
-template <bool kReuse>
+// Outputs are stored, and reused pixels loaded, by agent-scope accesses
+// (another workgroup of the same launch may read, or have written, them).
 __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int B, int L, float gamma,
                                                         const BlockTables& tab, SplitLds& sh) {
     constexpr int NS = kSplitSlots;
@@ -141,25 +142,17 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
             kraw[j] = jb.mask[off];
             fraw[j] = jb.image[off];
             rp[j] = global_ptr(tab.rho_pow)[m * kS + c];
-            if constexpr (kReuse) {
-                earlier[j] = in[j] && (m < L || (m < L + B && c < L));
-                old[j] = __hip_atomic_load(jb.out + (earlier[j] ? off : 0), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-            }
+            earlier[j] = in[j] && (m < L || (m < L + B && c < L));
+            old[j] = __hip_atomic_load(jb.out + (earlier[j] ? off : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         uint64_t any = 0;
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
             const uint8_t k = in[j] ? kraw[j] : (uint8_t)0;
-            float f = k ? fraw[j] : 0.0f, w = k ? rp[j] : 0.0f;
-            bool takes = k != 0;
-            if constexpr (kReuse) {
-                const bool reused = earlier[j] && !k && jb.delta > 0.0f;
-                f = reused ? old[j] : f;
-                w = reused ? jb.delta * rp[j] : w;
-                takes = takes || reused;
-            }
-            any |= ballot(takes);
+            const bool reused = earlier[j] && !k && jb.delta > 0.0f;
+            const float f = k ? fraw[j] : reused ? old[j] : 0.0f;
+            const float w = k ? rp[j] : reused ? jb.delta * rp[j] : 0.0f;
+            any |= ballot(k != 0 || reused);
             sh.tile[(NS * q + j) * 64 + lane] = make_float2(f, w);
         }
         if (lane == 0) sh.known[q] = any != 0;
@@ -341,11 +334,8 @@ __device__ __forceinline__ void reconstruct_block_split(const BlockJob& jb, int 
     }
 
     // ---- compose (Sec. II): known pixels copied, unknown pixels Re g
-    if (writes) {
-        const float value = tknown ? tvalue : acc;
-        if constexpr (kReuse) __hip_atomic_store(jb.out + toff, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else jb.out[toff] = value;
-    }
+    if (writes)
+        __hip_atomic_store(jb.out + toff, tknown ? tvalue : acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace fsr

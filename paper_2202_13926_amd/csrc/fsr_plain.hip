@@ -1,8 +1,6 @@
 // fsr_plain.hip -- one-image FSR at S = 32: one workgroup of one wavefront
-// per block, or of four for the smallest images (fsr_block_split4.h).
-// Supports 8, 16 and 24 are in fsr_plain_sg.hip.
+// per block.  Supports 8, 16 and 24 are in fsr_plain_sg.hip.
 #include "fsr_block.h"
-#include "fsr_block_split4.h"
 
 namespace fsr {
 
@@ -14,21 +12,15 @@ __global__ __launch_bounds__(64, kDft == kDftSplitBf16 ? 4 : 2) void fsr_plain_s
                                      reinterpret_cast<uint2*>(lds + kLdsFloats));
 }
 
-// The same with kSplitWaves wavefronts per block (fsr_block_split4.h).
-__global__ __launch_bounds__(64 * kSplitWaves) void fsr_plain_split_s32(PlainLaunch p) {
-    __shared__ __align__(16) SplitLds sh;
-    const int64_t blk = xcd_runs(blockIdx.x, p.n_blocks);
-    reconstruct_block_split<false>(plain_job(p, blk), p.block, p.border, p.gamma, p.tab, sh);
-}
-
-// Four wavefronts per block only on the null stream.  A workgroup of four needs
-// slots on all four SIMDs of a compute unit and 51 KiB of its LDS at one time,
-// which another stream's large launch does not leave until its last blocks run,
-// while workgroups of one wavefront take single slots as they come free.  us
-// until a 64 x 64 frame is done beside 1080p frames on another stream: with one
-// wavefront per block 108, with four 2125; alone 47.1 and 36.2.  A caller that
-// names a stream of its own may mean to overlap; work on the null stream waits
-// for other streams anyway, but for non-blocking ones.
+// One wavefront per block for the smallest images too.  Four (the routine of
+// the sequential variant, fsr_block_split4.h) take a 64 x 64 frame alone from
+// 47.1 to 36.2 us, but such a workgroup needs slots on all four SIMDs of a
+// compute unit and 51 KiB of its LDS at one time, which another stream's large
+// launch does not leave until its last blocks run, while workgroups of one
+// wavefront take single slots as they come free: sent while a 1080p frame of
+// 10.9 ms runs on another stream, the frame is done after 9.9 ms with four and
+// after 0.28 ms with one.  Which streams overlap cannot be told from the call's
+// own: the null stream too runs beside non-blocking ones.
 hipError_t launch_plain(const PlainLaunch& p, hipStream_t stream) {
     if (p.n_blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)p.n_blocks), block(64);
@@ -38,8 +30,6 @@ hipError_t launch_plain(const PlainLaunch& p, hipStream_t stream) {
         hipLaunchKernelGGL((fsr_plain_s32<kDftFft32, kArgmaxLds>), grid, block, 0, stream, p);
     } else if (p.dft == kDftSplitBf16) {
         hipLaunchKernelGGL((fsr_plain_s32<kDftSplitBf16, kArgmaxWave>), grid, block, 0, stream, p);
-    } else if (p.n_blocks <= kSplitMaxBlocks && stream == nullptr) {
-        hipLaunchKernelGGL(fsr_plain_split_s32, grid, dim3(64 * kSplitWaves), 0, stream, p);
     } else {
         hipLaunchKernelGGL((fsr_plain_s32<kDftFft32, kArgmaxWave>), grid, block, 0, stream, p);
     }

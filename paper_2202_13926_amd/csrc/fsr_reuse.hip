@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void fsr_reuse_split4_s32(PlainLa
     jb.out += f * frame_stride;
     if (jb.log != nullptr) jb.log += f * log_stride;
     jb.delta = delta;
-    reconstruct_block_split<true>(jb, p.block, p.border, p.gamma, p.tab, sh);
+    reconstruct_block_split(jb, p.block, p.border, p.gamma, p.tab, sh);
 }
 
 // ---- All blocks in one launch: a workgroup takes a block row of a frame and
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void fsr_reuse_rows_s32(PlainLaun
             jb.out += f * frame_stride;
             if (jb.log != nullptr) jb.log += f * log_stride;
             jb.delta = delta;
-            reconstruct_block_split<true>(jb, p.block, p.border, p.gamma, p.tab, sh);
+            reconstruct_block_split(jb, p.block, p.border, p.gamma, p.tab, sh);
             if (threadIdx.x < 64) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the outputs have arrived
                 if (threadIdx.x == 0) __hip_atomic_store(mine, bx + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
