@@ -170,12 +170,13 @@ FSR_API fsr_status fsr_reconstruct(fsr_context *ctx, const float *image, const u
  * (nbx - 1) + (r + 1)(nby - 1) + 1 steps (1,825 for 1920 x 1080 at B = 4,
  * L = 14), each of at most min(nby, ceil(nbx / (r + 1))) blocks per frame, so
  * the call is bound by the latency of one block per step rather than by
- * throughput.  Where no step has more than 512 blocks (over all frames) the
- * call is one launch: a workgroup of four wavefronts takes a row of blocks and
- * waits for the row above by a counter in device memory, which the call takes
- * from the stream's memory pool and gives back.  Under stream capture, when
- * that memory cannot be had, or with larger steps, there is one launch per
- * step, of four wavefronts per block up to 512 blocks and one above.  The
+ * throughput.  With at least 8 steps, none of them of more than 512 blocks
+ * (over all frames), the call is one launch: a workgroup of four wavefronts
+ * takes a row of blocks and waits for the row above by a counter in device
+ * memory, which the call takes from the device's memory pool in the stream's
+ * order and gives back.  Under stream capture, when that memory cannot be had,
+ * or with fewer or larger steps, there is one launch per step, of four
+ * wavefronts per block up to 512 blocks and one above.  The
  * result is bitwise the same.  S = 32, FSR_DFT_FP32, no flags
  * (FSR_ERR_UNSUPPORTED otherwise); a reuse_weight outside [0, 1] or NaN is
  * FSR_ERR_INVALID_ARG.

@@ -140,6 +140,14 @@ __global__ __launch_bounds__(64 * kSplitWaves) void fsr_reuse_rows_s32(PlainLaun
 // Rows of a call that the queue takes (4 MiB of counters).
 constexpr int64_t kMaxQueueRows = int64_t(1) << 20;
 
+// Calls of fewer steps than this go out as one launch per step: the queue's
+// counters, their reset and the second launch take some 20 us before the first
+// block.  us a call at I = 0 / 25 / 100, one launch per step and rows: 1 block
+// 20.4 / 28.0 / 51.5 and 41 / 43.3 / 62.1, a row of 4 33.5 / 64.3 / 157.9 and
+// 44.5 / 73.8 / 165.5, of 6 42.4 / 88.5 / 228.8 and 48.9 / 95.9 / 233.3, of 8
+// 74.7 / 116.9 / 303.0 and 55.5 / 115.5 / 301.7.
+constexpr int64_t kMinRowSteps = 8;
+
 // At most `widest` rows can make progress at one time; a workgroup that ends
 // its row takes the next.  So the grid holds that many: a workgroup per row
 // would hold LDS and wavefront slots for rows that cannot start yet, on every
@@ -186,7 +194,8 @@ hipError_t launch_reuse(const PlainLaunch& p, float delta, int32_t n_frames, int
     const int64_t steps = reuse_steps(p.img.height, p.img.width, B, p.border);
     const int64_t log_stride = p.n_blocks * (int64_t)p.img.iterations;
     const int64_t widest = std::min(nby, (nbx + slope - 1) / slope) * n_frames;
-    if (may_allocate && widest <= kSplitMaxBlocks && nby * n_frames <= kMaxQueueRows) {
+    const int64_t launches = std::min(steps, nbx * nby);   // steps that hold a block
+    if (may_allocate && launches >= kMinRowSteps && widest <= kSplitMaxBlocks && nby * n_frames <= kMaxQueueRows) {
         const hipError_t e = launch_reuse_rows(p, delta, n_frames, (int32_t)nby, (int32_t)slope,
                                                (int32_t)widest, frame_stride, log_stride, stream);
         if (e != hipErrorOutOfMemory) return e;
