@@ -300,8 +300,9 @@ FSR_API fsr_status fsr_batch_autotune(fsr_context *ctx, const fsr_image_desc *de
  * JSON of the form
  *   {"format": "fsr-batch-tuning-1", "arch": "<gcnArchName>", "cus": <CUs>,
  *    "entries": [[<size-class key>, waves_per_group, chunk, groups_per_cu], ...]}
- * where the key packs log2 of the batch's work, the support, the dft mode
- * and the largest iteration count.  Export writes a NUL-terminated string
+ * where the key packs log2 of the batch's work, the support, the dft mode,
+ * the largest iteration count and, for S = 8 with block <= 4, whether the
+ * batch is so small that it runs one block per wavefront.  Export writes a NUL-terminated string
  * of *len bytes (NUL included) into buf when cap suffices (buf NULL: only
  * *len is set; cap too small: FSR_ERR_INVALID_ARG with *len set).  Import
  * reads exactly that form, checks every schedule as fsr_reconstruct_batched

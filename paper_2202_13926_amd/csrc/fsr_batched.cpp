@@ -123,13 +123,16 @@ fsr_status plan_batch(const fsr_image_desc* descs, int32_t n, const fsr_params* 
 }
 
 // Key of the tuned-schedule table: log2 of the batch's work, the support
-// size and the DFT mode (the kernels differ in register and LDS use) and the
-// largest iteration count.
+// size and the DFT mode (the kernels differ in register and LDS use), the
+// largest iteration count, and whether the batch is too small for the eight
+// blocks per wavefront that its parameters admit (another kernel again, whose
+// chunks count blocks instead of units of eight).
 uint64_t size_class(const PlanTotals& plan, const fsr_params& params) {
     uint64_t w = 0;
     for (double x = plan.work; x >= 2.0; x /= 2.0) ++w;
-    const uint64_t S = (uint64_t)(params.block + 2 * params.border);
-    return (w << 48) | (S << 40) | ((uint64_t)(uint32_t)params.dft << 32) |
+    const int32_t S = params.block + 2 * params.border;
+    const uint64_t lone = plan.unit < blocks_per_wave(S, params.block, INT64_MAX) ? 1 : 0;
+    return (w << 48) | (lone << 47) | ((uint64_t)S << 40) | ((uint64_t)(uint32_t)params.dft << 32) |
            (uint64_t)(uint32_t)plan.max_iterations;
 }
 
