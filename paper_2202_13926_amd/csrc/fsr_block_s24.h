@@ -3,8 +3,8 @@
 //
 // Layout: lane = 8 a + b (a, b < 8), slot s = 3 i + j (i, j < 3); slot s of
 // lane (a, b) holds pixel, or bin, (a + 8 i, b + 8 j): the 576 bins fill
-// 64 lanes x 9 slots, where the generic layout of fsr_block_sg.h (one column
-// per lane) leaves 16 lanes idle at this size.
+// 64 lanes x 9 slots, where the layout of fsr_block_sg.h (one column
+// per lane) would leave 16 lanes idle.
 //
 // Argmax ties (Eq. 8: equal objectives go to the smaller bin k S + l).  The
 // bin index 192 i + 24 a + 8 j + b does not order as (slot, lane), so the
@@ -80,6 +80,21 @@ __device__ __forceinline__ void s24_codes(int a, int b, uint32_t (&code)[S24::NS
     }
     *map_lo = (uint32_t)m;
     *map_hi = (uint32_t)(m >> 32);
+}
+
+// q mod 24 for the target model's phase index 0 <= q < 2 S^2, by a multiply-
+// shift division; the product fits the full-rate 24-bit multiplier.
+constexpr uint32_t kMod24Magic = (65536u + 23) / 24;
+
+constexpr bool mod24_exact() {
+    for (uint32_t q = 0; q < 2u * 24 * 24; ++q)
+        if (q - 24 * ((q * kMod24Magic) >> 16) != q % 24) return false;
+    return true;
+}
+static_assert(mod24_exact(), "division by multiply-shift must be exact");
+
+__device__ __forceinline__ int mod24(int q) {
+    return q - 24 * (int)((uint32_t)mul_u24((int)kMod24Magic, q) >> 16);
 }
 
 // A lane's twiddles of one pass, for the element index p it holds: W24^p,
@@ -382,7 +397,7 @@ __device__ __forceinline__ void reconstruct_block_s24(const BlockJob& jb, int B,
 #pragma unroll
                 for (int s = 0; s < NS; ++s) w[s] = wrows[s / 3][8 * (s % 3)];
                 // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target
-                const int q4 = 4 * mod_small<S>(dot2_u16(u | (v << 16), tmn));
+                const int q4 = 4 * mod24(dot2_u16(u | (v << 16), tmn));
                 const float er = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_re));
                 const float ei = __int_as_float(__builtin_amdgcn_ds_bpermute(q4, tw_im));
                 acc = fmaf(cr, er, acc);

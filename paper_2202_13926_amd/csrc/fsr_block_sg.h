@@ -46,31 +46,8 @@ struct SgShape {
     static constexpr int kLoopFloats = kFullDup ? 8 * S * S : 4 * S * S;
     // ... and the S twiddles of the target model
     static constexpr int kLdsFloats = kLoopFloats + 2 * S;
-    static constexpr uint32_t kModMagic = (65536u + S - 1) / S;
-    static_assert(S % 2 == 0 && S >= 8 && S < 32 && S % G == 0, "even S in [8, 32)");
-    static_assert(NS <= 16, "slot code fits in 4 bits");
+    static_assert(S == 8 || S == 16, "every lane holds NS <= 4 pixels, phases reduce by a mask");
 };
-
-// q mod S for 0 <= q < 2 S^2 (the target-model phase index): a mask for
-// powers of two, else a multiply-shift division checked at compile time.
-template <int S>
-constexpr bool mod_magic_exact() {
-    for (uint32_t q = 0; q < 2u * S * S; ++q)
-        if (q - S * ((q * SgShape<S>::kModMagic) >> 16) != q % S) return false;
-    return true;
-}
-
-template <int S>
-__device__ __forceinline__ int mod_small(int q) {
-    if constexpr ((S & (S - 1)) == 0) {
-        return q & (S - 1);
-    } else {
-        static_assert(mod_magic_exact<S>(), "division by multiply-shift must be exact");
-        // q < 2 S^2 and the magic number are below 2^12 and 2^16: the
-        // product fits the full-rate 24-bit multiplier
-        return q - S * (int)((uint32_t)mul_u24((int)SgShape<S>::kModMagic, q) >> 16);
-    }
-}
 
 // 2D DFT of the real values v (slot s = pixel (G s + h, c)) into (re, im)
 // (slot s = bin (G s + h, c)).  `ftab` is the DFT table in LDS, `scr` the
@@ -249,7 +226,6 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
 
     // ---- gather and weighting: slot s holds pixel (G s + h, c)
     float xr[NS], wr[NS];
-    static_assert(G * S == 64, "every lane holds pixels");
     const uint64_t any_known = gather_support<S>(jb, y0, x0, h, c, [](int s) { return G * s; },
                                                  [](int) { return 0; }, tab.rho_pow, xr, wr);
 
@@ -367,9 +343,8 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
         // re-derive them inside the loop)
         const int lbase = opaque(8 * (h * P + (kFullDup ? c : 0)));   // entry (h, c), or row h
         // the target pixel's (m, n) packed for the phase index u m + v n,
-        // scaled by 8 (the table's byte address) where a mask reduces it
-        constexpr int kQs = (S & (S - 1)) == 0 ? 8 : 1;
-        const int tmn = opaque((kQs * tm) | ((kQs * tn) << 16));
+        // scaled by 8 (the table's byte address)
+        const int tmn = opaque((8 * tm) | ((8 * tn) << 16));
         const int c8 = opaque(8 * c);
         const char* wbytes = reinterpret_cast<const char*>(wtab);
         wave_sync();
@@ -427,28 +402,20 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                 }
                 const int u = G * slot + ln / S, v = ln % S;
                 const int idx = u * S + v;
-                // the winner's slot is uniform: with few slots, branch on it
-                // (scalar) and read two fixed registers instead of selecting
-                // among the slots on the vector ALUs; with many, the compiler's
-                // relative move is cheaper than the branches
+                // the winner's slot is uniform: branch on it (scalar) and read
+                // two fixed registers instead of selecting among the slots on
+                // the vector ALUs
                 float pr = 0.0f, pim = 0.0f;
-                if constexpr (NS <= 4) {
 #pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        if (slot == s) read_lowest(won, xr[s], xi[s], pr, pim);
-                    }
-                } else {
-                    pr = readlane_f(xr[slot], ln);
-                    pim = readlane_f(xi[slot], ln);
+                for (int s = 0; s < NS; ++s) {
+                    if (slot == s) read_lowest(won, xr[s], xi[s], pr, pim);
                 }
                 const float cr = gi * pr, ci = gi * pim;    // gamma * p (Eqs. 10-11)
 
                 // model: g += gamma p exp(+j 2 pi (u m + v n) / S) on the target,
                 // the twiddle read as one table entry: a lane exchange for each
                 // of its parts took 886 against 872 us per 1080p frame at S = 16
-                int q8;
-                if constexpr ((S & (S - 1)) == 0) q8 = dot2_u16(u | (v << 16), tmn) & (8 * S - 8);
-                else q8 = 8 * mod_small<S>(dot2_u16(u | (v << 16), tmn));
+                const int q8 = dot2_u16(u | (v << 16), tmn) & (8 * S - 8);
                 const float2 e2 = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(twt) + q8);
                 const float er = e2.x, ei = e2.y;
                 acc = fmaf(cr, er, acc);
@@ -461,15 +428,11 @@ __device__ __forceinline__ void reconstruct_block_sg(const BlockJob& jb, int B, 
                 const float2* wrow;
                 if constexpr (kFullDup) {
                     wrow = reinterpret_cast<const float2*>(wbytes + lbase + 8 * ((S - u) * P + (S - v)));
-                } else if constexpr ((S & (S - 1)) == 0) {
+                } else {
                     // the row offset is a multiple of 8 S, the wrapped column
                     // offset 8 ((c - v) mod S) lies below it
                     const int col8 = (c8 - 8 * v) & (8 * S - 8);
                     wrow = reinterpret_cast<const float2*>(wbytes + ((lbase + 8 * (S - u) * P) | col8));
-                } else {
-                    int col = c - v;
-                    col += col < 0 ? S : 0;
-                    wrow = reinterpret_cast<const float2*>(wbytes + lbase + 8 * ((S - u) * P + col));
                 }
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
