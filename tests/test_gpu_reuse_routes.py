@@ -4,6 +4,8 @@ run as rows in one launch, unless the device's memory pool refuses the rows'
 counters; larger steps are one launch each.  Results on every route are bitwise
 those of one launch per step, which stream capture always records.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -76,3 +78,41 @@ def test_route_and_result(n, h, w, want):
     if n > 1:             # a frame alone, which may take another route
         alone = fsr.reconstruct_reuse(clip.images[-1], clip.masks[-1], clip.params, 0.5, ctx=clip.ctx)
         assert torch.equal(a[0][-1], alone)
+
+
+class MemPoolProps(ctypes.Structure):
+    """hipMemPoolProps: pinned allocations on device 0, at most max_size bytes."""
+    _fields_ = [("alloc_type", ctypes.c_int), ("handle_types", ctypes.c_int), ("location_type", ctypes.c_int),
+                ("location_id", ctypes.c_int), ("security", ctypes.c_void_p), ("max_size", ctypes.c_size_t),
+                ("reserved", ctypes.c_ubyte * 56)]
+
+
+def test_pool_without_room():
+    """The counters cannot be allocated: one launch per step, no error left."""
+    print("\n[gpu case] reuse routes: a memory pool without room for the counters", flush=True)
+    clip = Clip(2, 5, 9, 7, 960)
+    ref = clip.captured()
+    clip.call()
+    clip.take()
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    old, pool, ptr = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipDeviceGetMemPool(ctypes.byref(old), 0) == 0
+    props = MemPoolProps(1, 0, 1, 0, None, 128)
+    assert hip.hipMemPoolCreate(ctypes.byref(pool), ctypes.byref(props)) == 0
+    assert hip.hipDeviceSetMemPool(0, pool) == 0
+    try:
+        assert hip.hipMallocAsync(ctypes.byref(ptr), ctypes.c_size_t(256), None) != 0   # it does refuse
+        hip.hipGetLastError()
+        names = kernels_of(clip.call)
+        left = hip.hipGetLastError()
+        got = clip.take()
+    finally:
+        assert hip.hipDeviceSetMemPool(0, old) == 0
+        torch.cuda.synchronize()
+        assert hip.hipMemPoolDestroy(pool) == 0
+    assert names == 29 * ["fsr_reuse_split4_s32"] and left == 0
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    assert kernels_of(clip.call) == ROWS
+    again = clip.take()
+    assert torch.equal(again[0], ref[0]) and torch.equal(again[1], ref[1])
