@@ -387,11 +387,10 @@ typedef struct fsr_server fsr_server;
  * second one starts beside it on the other compute stream only if it is at
  * most a quarter of the running batch's work.  A pinned host frame of more
  * than 4 MiB that reaches an idle server is copied in two parts and launched
- * by itself, in two launches, the first behind the first part.  The compute
- * streams are
- * created with a CU mask enabling every compute unit (each then has a
- * hardware queue of its own) and therefore synchronise with the legacy null
- * stream.
+ * by itself, in two launches, the first behind the first part (the statistics
+ * count them as one).  The compute streams are created with a CU mask enabling
+ * every compute unit (each then has a hardware queue of its own) and therefore
+ * synchronise with the legacy null stream.
  */
 FSR_API fsr_status fsr_server_create(fsr_context *ctx, const fsr_params *params,
                                      const fsr_server_config *cfg, fsr_server **out);

@@ -305,8 +305,9 @@ def _log_arg(argmax_log, H, W, params):
 
 def fsr_reconstruct_reuse(ctx: Context, image, mask, out, params: fsr_params, reuse_weight: float,
                           argmax_log=None, stream=None) -> None:
-    """Enqueue the sequential variant that reuses reconstructed pixels (one
-    launch per wavefront step) on ``stream``."""
+    """Enqueue the sequential variant that reuses reconstructed pixels on
+    ``stream`` (rows of blocks in one launch, or one launch per wavefront step;
+    see include/fsr.h)."""
     H, W, stride = _image_args(image, mask, out)
     log_ptr = _log_arg(argmax_log, H, W, params)
     _check(load_library().fsr_reconstruct_reuse(

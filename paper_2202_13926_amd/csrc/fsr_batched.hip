@@ -7,8 +7,9 @@
 // forms (fsr_batched_grid_sg, fsr_batched_sg); at S = 8 with B <= 4 and more
 // than a few thousand blocks (blocks_per_wave) a wavefront takes units of
 // eight blocks of one image (fsr_batched_grid_multi, fsr_batched_multi), every
-// image's block range then being padded to a multiple of eight.  Each block runs the same arithmetic as in the one-image
-// kernel, so its result does not depend on the batch it is part of.
+// image's block range then being padded to a multiple of eight.  Each block
+// runs the same arithmetic as in the one-image kernel, so its result does not
+// depend on the batch it is part of.
 #include "fsr_batch_internal.h"
 #include "fsr_block.h"
 #include "fsr_block_multi.h"

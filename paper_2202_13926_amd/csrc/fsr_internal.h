@@ -47,7 +47,11 @@ struct ImageDesc {
 // Measured at I = 100, us a call with 1 and 8 blocks per wavefront: 256 blocks
 // 18.7 and 35.5, 2025 21.5 and 35.7, 4096 27.7 and 36.2, 5184 34.8 and 36.5,
 // 8100 41.9 and 37.1; with B = 2, 256 blocks 18.6 and 32.2, 4096 27.8 and 33.4,
-// 5184 34.8 and 33.3.
+// 5184 34.8 and 33.3.  Calls side by side share the slots, and near the line
+// four streams at once are then better served by eight: us a call on 1 / 2 / 4
+// streams of 1024 blocks 20.6 / 10.4 / 7.5 and 36.9 / 20.4 / 12.2, of 2116 24.1 /
+// 14.1 / 9.0 and 37.7 / 21.0 / 13.0, of 4096 28.0 / 17.4 / 15.9 and 38.1 / 21.3 /
+// 13.4.
 constexpr int64_t kOnePerWaveMaxBlocks = 18 * 256;
 
 inline int32_t blocks_per_wave(int32_t support, int32_t block, int64_t n_blocks) {
