@@ -208,12 +208,15 @@ __device__ __forceinline__ void queue_body(const BatchLaunch& p, float* lds) {
     }
 }
 
-// Four wavefronts per SIMD, as many as the LDS allows, although the split-bf16
-// form would take 136 registers and the persistent ones 145 and 158 (spills of
-// at most 120 bytes outside the iterations).  us for a 1080p frame at I = 100,
-// without and with the bound: split-bf16 grid 3169 and 2994; persistent with
-// chunk 4 and 16 workgroups per compute unit 2954 and 2818, split-bf16 3237 and
-// 3173 (at 10 workgroups per compute unit 3287 and 3296).
+// Registers for four wavefronts per SIMD, as many as the LDS allows, although
+// the split-bf16 forms would take 136 and 158 (spills of at most 120 bytes
+// outside the iterations).  us for a 1080p frame at I = 100, without and with the
+// bound: split-bf16 grid 3169 and 2994, persistent with chunk 4 and 16 workgroups
+// per compute unit 3237 and 3173.  Not for the persistent FP32 form, which would
+// take 145: there the frame gains (2970 and 2810), but batches that leave the
+// device room lose, as more of their wavefronts share a SIMD (chunk 4, two
+// workgroups of four wavefronts per compute unit, 2048 blocks 219 and 263; four
+// of four, 4096 blocks 303 and 356).
 template <int kWaves, int kDft>
 __global__ __launch_bounds__(64 * kWaves, 4) void fsr_batched_grid_s32(BatchLaunch p) {
     __shared__ __align__(16) float lds[kWaves * kLdsFloats];
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void fsr_batched_grid_s32(BatchLaun
 }
 
 template <int kWaves, int kDft>
-__global__ __launch_bounds__(64 * kWaves, 4) void fsr_batched_s32(BatchLaunch p) {
+__global__ __launch_bounds__(64 * kWaves, kDft == kDftSplitBf16 ? 4 : 1) void fsr_batched_s32(BatchLaunch p) {
     __shared__ __align__(16) float lds[kWaves * kLdsFloats];
     queue_body<kWaves, kS, kDft>(p, lds);
 }

@@ -50,3 +50,14 @@ def test_split_bf16_loop_beside_fp32(ctx):
                    lambda: fsr.fsr_reconstruct(ctx, img, mask, out, bf16))
     print(f"\n[gpu case] 1024 blocks, I = 200: FP32 {a:.1f} us, split-bf16 {b:.1f} us", flush=True)
     assert b <= 1.09 * a
+
+
+def test_queue_schedule_spreads_small_batches(ctx):
+    """Four blocks per wavefront in turn, 64 and 512 wavefronts on 1024 SIMDs:
+    both are bound by the latency of four blocks, so the larger batch may take
+    1.1 times the smaller."""
+    p, ws, sched = fsr.make_params(iterations=100), fsr.Workspace(1, DEV), fsr.make_schedule(4, 4, 2)
+    batches = [[fsr.BatchItem(*frame(*blocks), 100)] for blocks in ((16, 16), (32, 64))]
+    a, b = best_us(*(lambda items=items: fsr.fsr_reconstruct_batched(ctx, items, p, ws, sched) for items in batches))
+    print(f"\n[gpu case] queue schedule, 256 blocks {a:.1f} us, 2048 blocks {b:.1f} us", flush=True)
+    assert b <= 1.1 * a
